@@ -170,6 +170,11 @@ struct Ctx {
     int chol_w[2] = {0, 0};     // their lower bandwidths
     DBuf info;
     DBuf vz1;                   // EXP_finite Z1 scratch
+    // resident runs: exchanged cells and partials (cleared when allocated, words numbered on
+    // from run to run), and whether they are still tried
+    DBuf res_cells, res_slots;
+    unsigned res_epoch = 0;
+    bool res_off = false;
     BicgState *host_state = nullptr;  // pinned; 3 slots (synchronous reads, pipelined polls)
     double *host_scal = nullptr;      // pinned
     hipEvent_t poll_ev[2] = {nullptr, nullptr};
@@ -187,6 +192,9 @@ struct Ctx {
         q.release(); qs.release(); ubest.release(); xp.release(); bp.release();
         part_a.release(); part_b.release(); state.release(); scal.release();
         chol[0].release(); chol[1].release(); info.release(); vz1.release();
+        res_cells.release(); res_slots.release();
+        res_epoch = 0;
+        res_off = false;
         if (host_state) (void)hipHostFree(host_state);
         for (hipEvent_t &e : poll_ev) {
             if (e) (void)hipEventDestroy(e);
@@ -388,6 +396,7 @@ int setup_levels(int n_finest, int n_levels, int bc, int dim) {
     // sweep (one per tile)
     CKR(c.part_b.ensure((size_t)2 * std::max(4096, maxblk) * sizeof(Pair)));
     CKR(c.state.ensure(sizeof(BicgState)));
+    CKH(hipMemsetAsync(c.state.p, 0, sizeof(BicgState), g_stream));
     CKR(c.scal.ensure(64 * sizeof(double)));
     CKR(c.info.ensure(64));
     const long long nz1 =
@@ -699,6 +708,85 @@ int window_graph(const Level &L, TX *x, int K, hipGraphExec_t *out, int defer = 
     return EXCMG_OK;
 }
 
+// The whole run in one resident launch, on grids whose vectors fit on the chip (plain
+// Algorithm 2, contiguous rows, no explicit choice of the sweeps' form and no timing of
+// them).  *done = false: not taken (or given up, with nothing changed), and the
+// launch-per-sweep form runs.
+template <typename T>
+int bicg_resident(const Level &L, double *x, BicgState &hs, bool *done) {
+    Ctx &c = g_ctx;
+    *done = false;
+    if (c.res_off || c.dim != 3 || g_cg || g_var.d || g_var.xs || g_timing || g_rq_min > 0 ||
+        (sizeof(T) == 4 && L.ld != L.n) || hs.status != kRunning)
+        return EXCMG_OK;
+    ResidentPlan plan;
+    if (!resident_plan(L.n, sizeof(T) == 8, plan)) return EXCMG_OK;
+    const size_t cell_bytes = std::max((size_t)16, plan.exchange), slot_bytes = 6 * 256 * 16;
+    const unsigned steps = (unsigned)std::max(0, hs.maxit - hs.iter) + 2;
+    const bool wrap = c.res_epoch + steps < c.res_epoch;
+    if (wrap || c.res_cells.bytes < cell_bytes || c.res_slots.bytes < slot_bytes) {
+        if (c.res_cells.ensure(cell_bytes) != EXCMG_OK || c.res_slots.ensure(slot_bytes) != EXCMG_OK) {
+            g_err[0] = 0;      // (no room: the sweeps need none)
+            c.res_off = true;
+            return EXCMG_OK;
+        }
+        CKH(hipMemsetAsync(c.res_cells.p, 0, c.res_cells.bytes, g_stream));
+        CKH(hipMemsetAsync(c.res_slots.p, 0, c.res_slots.bytes, g_stream));
+        c.res_epoch = 0;
+    }
+    ResidentRun<T> run{};
+    run.n = L.n;
+    run.nbx = plan.nbx;
+    run.nby = plan.nby;
+    run.bx = plan.bx;
+    run.by = plan.by;
+    run.bz = plan.bz;
+    run.sgn = L.g1.sgn;
+    run.r = c.r.as<T>();
+    run.rs = c.rs.as<T>();
+    for (int k = 0; k < 2; k++) {
+        run.p[k] = c.p[k].as<T>();
+        run.ps[k] = c.ps[k].as<T>();
+    }
+    run.x = x;
+    run.x_work = c.q.as<double>();
+    run.state = c.state.as<BicgState>();
+    run.part = c.part_b.as<Pair>();
+    run.part_count = b_partials<double, T>(L);
+    run.cells = c.res_cells.p;
+    run.slots = c.res_slots.p;
+    run.epoch = c.res_epoch;
+    if (resident_run<T>(plan, run, g_stream) != hipSuccess) {
+        (void)hipGetLastError();
+        c.res_off = true;
+        return EXCMG_OK;
+    }
+    const int iter0 = hs.iter;
+    BicgState now;
+    CKR(read_state(now));
+    if (now.err) {
+        // a wait ran out (the device was not the run's own): the launch-per-sweep form from
+        // here on.  x, r and r* are as they were; a resumed run's directions may not be, and
+        // it ends as a breakdown does, which starts a fresh run
+        c.res_off = true;
+        if (hs.iter > 0) {
+            hs.status = kBreakdown;
+            *done = true;
+        }
+        hs.err = 0;
+        *c.host_state = hs;
+        CKH(hipMemcpyAsync(c.state.p, c.host_state, sizeof(BicgState), hipMemcpyHostToDevice,
+                           g_stream));
+        CKH(hipStreamSynchronize(g_stream));
+        return EXCMG_OK;
+    }
+    c.res_epoch += (unsigned)(now.iter - iter0) + 2;
+    CKH((copy_convert<double, double>(L.nu, run.x_work, x, g_stream)));
+    hs = now;
+    *done = true;
+    return EXCMG_OK;
+}
+
 // Iterations of Algorithm 2 on level L after bicg_start: the Bi-CG vectors r, r*, p, p*, q, q*
 // have type T, the iterate x type TX.  Every kernel returns at once when the run has stopped,
 // so the host issues K iterations between two polls of the state: directly, or (in solves)
@@ -707,6 +795,9 @@ int window_graph(const Level &L, TX *x, int K, hipGraphExec_t *out, int defer = 
 // continues at the j it stopped at, with its search directions).
 template <typename TX, typename T>
 int bicg_iterate(const Level &L, TX *x, BicgState &hs, long long &j) {
+    bool done = false;
+    if constexpr (sizeof(TX) == 8) CKR(bicg_resident<T>(L, x, hs, &done));
+    if (done) return EXCMG_OK;
     int K = poll_interval(L.nu, g_ctx.dim);
     K += K & 1;
     if (g_timing) CKR(ensure_events(4 * (size_t)(K + 1)));

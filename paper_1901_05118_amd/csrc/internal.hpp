@@ -59,6 +59,7 @@ struct BicgState {
     double rho_slot[2];  // rho_j in slot j & 1 (steps with folded finalisations)
     double alpha_slot[2];  // alpha_j in slot j & 1 (update sweeps that apply the updates of
                            // two iterations to the iterate read alpha_{j-1} from it)
+    int err;               // set by a resident run that gave up (see resident.hip)
 };
 
 // A sweep that folds in the finalisation of the preceding sweep (see step.hpp).  state ==
@@ -210,6 +211,35 @@ hipError_t copy_convert(long long n, const TS *src, TD *dst, hipStream_t st);
 hipError_t bicg_start(BicgState *s, const Pair *rr_part, int count, double eps, int maxit,
                       hipStream_t st);   // rr = rho = r.r (r* = r), bb precomputed
 hipError_t reduce_to(double *out, const Pair *part, int count, int slot, hipStream_t st);
+
+// ---------------------------------------------------------------- resident runs
+
+// A whole Bi-CG run in one cooperative launch (resident.hip): nbx x nby x nbz bricks of
+// bx x by x bz cells, one per workgroup, C consecutive z-cells per thread.
+struct ResidentPlan {
+    int nbx = 0, nby = 0, nbz = 0, bx = 0, by = 0, bz = 0, C = 0;
+    int rs = 0;                    // row stride of the LDS box
+    int threads = 0, blocks = 0;
+    size_t lds = 0, exchange = 0;  // bytes of LDS; of exchanged cells
+};
+template <typename T>
+struct ResidentRun {
+    int n, nbx, nby, bx, by, bz;
+    double sgn;                    // fictitious-point sign (Geom::sgn)
+    const T *r, *rs;               // residuals at the start (or at a resumption)
+    T *p[2], *ps[2];               // directions: read at a resumption, written at the end
+    const double *x;               // iterate at the start
+    double *x_work;                // iterate of the run (the caller's is left alone)
+    BicgState *state;              // as bicg_start or state_resume left it
+    const Pair *part;              // resumption: partials of r*.r and r.r
+    int part_count;
+    void *cells;                   // exchanged cells (ResidentPlan::exchange bytes)
+    void *slots;                   // exchanged partials: 6 planes of 16 bytes per workgroup (256)
+    unsigned epoch;                // the run's exchanges are numbered from epoch + 1
+};
+bool resident_plan(int n, bool fp64, ResidentPlan &plan);
+template <typename T>
+hipError_t resident_run(const ResidentPlan &plan, const ResidentRun<T> &run, hipStream_t st);
 
 // ---------------------------------------------------------------- level kernels
 
