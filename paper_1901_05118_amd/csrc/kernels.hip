@@ -1,4 +1,4 @@
-// Streaming, reduction, transfer and direct-solve kernels of the EXCMG library (gfx950).
+// Streaming, reduction and right-hand-side kernels of the EXCMG library (gfx950).
 //
 // Every kernel here reproduces the arithmetic order its operation is specified with
 // (contraction off, sums left to right as the formulas are written), so results are
@@ -653,181 +653,6 @@ hipError_t from_nodes(int N, const double *u, double *x, hipStream_t st) {
     const i64 n = N - 1;
     hipLaunchKernelGGL(k_from_nodes, dim3((unsigned)((n * n * n + 255) / 256)), dim3(256), 0, st,
                        N, u, x);
-    return hipGetLastError();
-}
-
-// ------------------------------------------------------------------ EXP_finite
-
-// Phase 1: the value of every node of Z1 (grid of N1 = N/2 cells), by its place in the
-// interpolation cells of Z0 (N0 = N/4 cells): Step 1 for nodes of Z0, eq. (secfff); Step 2
-// for edge midpoints, eq. (bfsec); Step 3 for face centres, the mean of eq. (bfsec) on the
-// two face diagonals; Step 4 for cell centres, the mean on the four space diagonals.
-struct Z1Grid {
-    const double *u1, *u0;
-    int N1, N0;
-    __device__ __forceinline__ double U1(int a, int b, int c) const {
-        const i64 M = (i64)N1 + 1;
-        return u1[((i64)c * M + b) * M + a];
-    }
-    __device__ __forceinline__ double U0(int a, int b, int c) const {  // even Z1 coordinates
-        const i64 M = (i64)N0 + 1;
-        return u0[((i64)(c / 2) * M + b / 2) * M + a / 2];
-    }
-    // eq. (bfsec) at Z1 node m on the segment from corner e to corner f
-    __device__ __forceinline__ double bfsec(int ma, int mb, int mc, int ea, int eb, int ec,
-                                            int fa, int fb, int fc) const {
-        return U1(ma, mb, mc) +
-               (1.0 / 8.0) * (U1(ea, eb, ec) - U0(ea, eb, ec) + U1(fa, fb, fc) - U0(fa, fb, fc));
-    }
-};
-
-__global__ void __launch_bounds__(256) k_exp_finite_z1(Z1Grid z, double *v) {
-    const i64 M = (i64)z.N1 + 1;
-    const i64 total = M * M * M;
-    const i64 t = (i64)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= total) return;
-    const int a = (int)(t % M), b = (int)((t / M) % M), c = (int)(t / (M * M));
-    const int pa = a & 1, pb = b & 1, pc = c & 1;
-    const int odd = pa + pb + pc;
-    double val;
-    if (odd == 0) {
-        val = (5.0 * z.U1(a, b, c) - z.U0(a, b, c)) / 4.0;
-    } else if (odd == 1) {
-        if (pa) val = z.bfsec(a, b, c, a - 1, b, c, a + 1, b, c);
-        else if (pb) val = z.bfsec(a, b, c, a, b - 1, c, a, b + 1, c);
-        else val = z.bfsec(a, b, c, a, b, c - 1, a, b, c + 1);
-    } else if (odd == 2) {
-        if (!pc) {        // face normal to z: diagonals in x-y
-            val = (z.bfsec(a, b, c, a - 1, b - 1, c, a + 1, b + 1, c) +
-                   z.bfsec(a, b, c, a + 1, b - 1, c, a - 1, b + 1, c)) / 2.0;
-        } else if (!pb) { // face normal to y: diagonals in x-z
-            val = (z.bfsec(a, b, c, a - 1, b, c - 1, a + 1, b, c + 1) +
-                   z.bfsec(a, b, c, a + 1, b, c - 1, a - 1, b, c + 1)) / 2.0;
-        } else {          // face normal to x: diagonals in y-z
-            val = (z.bfsec(a, b, c, a, b - 1, c - 1, a, b + 1, c + 1) +
-                   z.bfsec(a, b, c, a, b + 1, c - 1, a, b - 1, c + 1)) / 2.0;
-        }
-    } else {
-        val = (z.bfsec(a, b, c, a - 1, b - 1, c - 1, a + 1, b + 1, c + 1) +
-               z.bfsec(a, b, c, a + 1, b - 1, c - 1, a - 1, b + 1, c + 1) +
-               z.bfsec(a, b, c, a - 1, b + 1, c - 1, a + 1, b - 1, c + 1) +
-               z.bfsec(a, b, c, a + 1, b + 1, c - 1, a - 1, b - 1, c + 1)) / 4.0;
-    }
-    v[t] = val;
-}
-
-// Phase 2 (Step 5): every node of Z2 (N cells) from the 27 Z1 values of its interpolation
-// cell by tri-quadratic Lagrange interpolation, eqs. (inter)-(iinter).  Along an axis the
-// local position a = 0..4 (in steps of h) has the weights l_0, l_1, l_2 at xi = a/4; even
-// positions select one node with weight 1.  Terms are summed in the node order of the cell
-// (z slowest, x fastest) and zero-weight terms are skipped, which leaves every sum unchanged.
-__constant__ double kLag[5][3] = {{1.0, 0.0, 0.0},
-                                  {0.375, 0.75, -0.125},
-                                  {0.0, 1.0, 0.0},
-                                  {-0.125, 0.75, 0.375},
-                                  {0.0, 0.0, 1.0}};
-
-__global__ void __launch_bounds__(256) k_exp_finite_z2(int N, const double *v, double *w) {
-    const i64 M = (i64)N + 1;
-    const i64 total = M * M * M;
-    const i64 t = (i64)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= total) return;
-    const int i = (int)(t % M), j = (int)((t / M) % M), k = (int)(t / (M * M));
-    const int N1 = N / 2, N0 = N / 4;
-    const i64 M1 = (i64)N1 + 1;
-    if (((i | j | k) & 1) == 0) {
-        w[t] = v[((i64)(k / 2) * M1 + j / 2) * M1 + i / 2];
-        return;
-    }
-    const int cx = min(i / 4, N0 - 1), cy = min(j / 4, N0 - 1), cz = min(k / 4, N0 - 1);
-    const int a = i - 4 * cx, b = j - 4 * cy, c = k - 4 * cz;
-    const int alo = (a & 1) ? 0 : a / 2, ahi = (a & 1) ? 2 : a / 2;
-    const int blo = (b & 1) ? 0 : b / 2, bhi = (b & 1) ? 2 : b / 2;
-    const int clo = (c & 1) ? 0 : c / 2, chi = (c & 1) ? 2 : c / 2;
-    double val = 0.0;
-    for (int ga = clo; ga <= chi; ga++)
-        for (int be = blo; be <= bhi; be++)
-            for (int al = alo; al <= ahi; al++) {
-                const double wgt = kLag[a][al] * kLag[b][be] * kLag[c][ga];
-                val = val + wgt * v[((i64)(2 * cz + ga) * M1 + (2 * cy + be)) * M1 + (2 * cx + al)];
-            }
-    w[t] = val;
-}
-
-hipError_t exp_finite(int N, const double *u1, const double *u0, double *v_scratch, double *w,
-                      hipStream_t st) {
-    Z1Grid z{u1, u0, N / 2, N / 4};
-    const i64 M1 = (i64)N / 2 + 1;
-    hipLaunchKernelGGL(k_exp_finite_z1, dim3((unsigned)((M1 * M1 * M1 + 255) / 256)), dim3(256), 0,
-                       st, z, v_scratch);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const i64 M = (i64)N + 1;
-    hipLaunchKernelGGL(k_exp_finite_z2, dim3((unsigned)((M * M * M + 255) / 256)), dim3(256), 0,
-                       st, N, v_scratch, w);
-    return hipGetLastError();
-}
-
-// ------------------------------------------------------------------ EXP_true
-
-// Coarse nodes: eq. (t1); edge midpoints of coarse cells: eq. (chenlin) along the edge; face
-// and cell centres: mean of eq. (chenlin) over the two face diagonals or four space
-// diagonals (the three-dimensional form of Steps 3-4).
-struct TrueGrid {
-    const double *uh, *u2h;
-    int N;
-    __device__ __forceinline__ double H(int i, int j, int k) const {
-        const i64 M = (i64)N + 1;
-        return uh[((i64)k * M + j) * M + i];
-    }
-    __device__ __forceinline__ double C(int i, int j, int k) const {  // even fine coordinates
-        const i64 M = (i64)N / 2 + 1;
-        return u2h[((i64)(k / 2) * M + j / 2) * M + i / 2];
-    }
-    __device__ __forceinline__ double chenlin(double mid, int ei, int ej, int ek, int fi, int fj,
-                                              int fk) const {
-        return mid + (1.0 / 6.0) * (H(ei, ej, ek) - C(ei, ej, ek) + H(fi, fj, fk) - C(fi, fj, fk));
-    }
-};
-
-__global__ void __launch_bounds__(256) k_exp_true(TrueGrid g, double *ut) {
-    const int N = g.N;
-    const i64 M = (i64)N + 1;
-    const i64 total = M * M * M;
-    const i64 t = (i64)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= total) return;
-    const int i = (int)(t % M), j = (int)((t / M) % M), k = (int)(t / (M * M));
-    const int oi = i & 1, oj = j & 1, ok = k & 1;
-    const double mid = g.H(i, j, k);
-    double v;
-    const int odd = oi + oj + ok;
-    if (odd == 0) {
-        v = (4.0 * mid - g.C(i, j, k)) / 3.0;
-    } else if (odd == 1) {
-        if (oi) v = g.chenlin(mid, i - 1, j, k, i + 1, j, k);
-        else if (oj) v = g.chenlin(mid, i, j - 1, k, i, j + 1, k);
-        else v = g.chenlin(mid, i, j, k - 1, i, j, k + 1);
-    } else if (odd == 2) {
-        if (!ok) v = (g.chenlin(mid, i - 1, j - 1, k, i + 1, j + 1, k) +
-                      g.chenlin(mid, i + 1, j - 1, k, i - 1, j + 1, k)) / 2.0;
-        else if (!oj) v = (g.chenlin(mid, i - 1, j, k - 1, i + 1, j, k + 1) +
-                           g.chenlin(mid, i + 1, j, k - 1, i - 1, j, k + 1)) / 2.0;
-        else v = (g.chenlin(mid, i, j - 1, k - 1, i, j + 1, k + 1) +
-                  g.chenlin(mid, i, j + 1, k - 1, i, j - 1, k + 1)) / 2.0;
-    } else {
-        v = (g.chenlin(mid, i - 1, j - 1, k - 1, i + 1, j + 1, k + 1) +
-             g.chenlin(mid, i + 1, j - 1, k - 1, i - 1, j + 1, k + 1) +
-             g.chenlin(mid, i - 1, j + 1, k - 1, i + 1, j - 1, k + 1) +
-             g.chenlin(mid, i + 1, j + 1, k - 1, i - 1, j - 1, k + 1)) / 4.0;
-    }
-    ut[t] = v;
-}
-
-hipError_t exp_true(int N, const double *uh, const double *u2h, double *ut, hipStream_t st) {
-    TrueGrid g{uh, u2h, N};
-    const i64 M = (i64)N + 1;
-    hipLaunchKernelGGL(k_exp_true, dim3((unsigned)((M * M * M + 255) / 256)), dim3(256), 0, st, g,
-                       ut);
     return hipGetLastError();
 }
 
