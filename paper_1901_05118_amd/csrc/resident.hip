@@ -423,22 +423,25 @@ __global__ void __launch_bounds__(MT) k_resident(ResidentRun<T> a) {
         }
     }
     unsigned ep = a.epoch;
+    // Phases of an iteration are kept apart in the registers: addresses and FP64 forms of FP32
+    // values that one phase derives are not carried into the next.
+    auto keep = [&]() {
+        asm volatile("" : "+v"(ob), "+v"(cells));
+        if constexpr (sizeof(T) == 4) {
+#pragma unroll
+            for (int c = 0; c < C; c++) asm volatile("" : "+v"(r[c]), "+v"(s[c]), "+v"(o[c]));
+        }
+        if (MULTI) {
+#pragma unroll
+            for (int q = 0; q < NH; q++) asm volatile("" : "+v"(hplace[q]), "+v"(hdest[q]));
+        }
+    };
 
     while (status == kRunning) {
         ep++;
-        // (keeps values derived from these out of the registers that live across iterations)
-        asm volatile("" : "+v"(ob), "+v"(cells), "+v"(tid));
+        asm volatile("" : "+v"(tid));
         const int lane = tid & 63, wave = tid >> 6;
-        // (and FP32 vectors in their own width)
-#pragma unroll
-        for (int c = 0; c < C; c++) asm volatile("" : "+v"(r[c]), "+v"(s[c]), "+v"(o[c]));
-        if (MULTI) {
-#pragma unroll
-            for (int q = 0; q < NH; q++) {
-                asm volatile("" : "+v"(hplace[q]), "+v"(hdest[q]));
-                asm volatile("" : "+v"(hr[q]), "+v"(hs[q]), "+v"(hv[q]));
-            }
-        }
+        keep();
         // ---- directions: p into LDS, p* into o and hv
         T ho[MULTI ? NH : 1];
         {
@@ -464,6 +467,7 @@ __global__ void __launch_bounds__(MT) k_resident(ResidentRun<T> a) {
             for (int q = 0; q < NH; q++) hv[q] = (T)((double)hs[q] + beta * (double)ho[q]);
         }
         __syncthreads();
+        keep();
 
         // ---- q = A p, sigma = p*.q
         T qv[C], qs[C];
@@ -471,6 +475,8 @@ __global__ void __launch_bounds__(MT) k_resident(ResidentRun<T> a) {
         column_outputs<C, RS, T>(M + (ob - 2 * PS - 2 * RS - 2), PS, [&](int c, double y) {
             qv[c] = c < cells ? (T)y : (T)0;
             dot2_acc(sg[0], (double)o[c], (double)qv[c]);
+            // (one output after the other)
+            if (C >= 8) asm volatile("" : "+v"(sg[0].s), "+v"(sg[0].c), "+v"(qv[c]));
         });
         wave_merge_n<1>(sg);
         if (lane == 0) red[wave] = sg[0];
@@ -488,11 +494,7 @@ __global__ void __launch_bounds__(MT) k_resident(ResidentRun<T> a) {
             }
         }
         // ---- p* into LDS, p into o and hv; q* = A^T p*
-        asm volatile("" : "+v"(ob), "+v"(cells));
-        if (MULTI) {
-#pragma unroll
-            for (int q = 0; q < NH; q++) asm volatile("" : "+v"(hplace[q]));
-        }
+        keep();
         {
             T pv[C];
 #pragma unroll
@@ -513,9 +515,12 @@ __global__ void __launch_bounds__(MT) k_resident(ResidentRun<T> a) {
             }
         }
         __syncthreads();
-        asm volatile("" : "+v"(ob));
+        keep();
         column_outputs<C, RS, T>(M + (ob - 2 * PS - 2 * RS - 2), PS,
-                                 [&](int c, double y) { qs[c] = c < cells ? (T)y : (T)0; });
+                                 [&](int c, double y) {
+                                     qs[c] = c < cells ? (T)y : (T)0;
+                                     if (C >= 8) asm volatile("" : "+v"(qs[c]));
+                                 });
         // (q* is formed here, before the wait, not carried over it as its 21 C terms)
 #pragma unroll
         for (int c = 0; c < C; c++) asm volatile("" : "+v"(qs[c]));
@@ -541,6 +546,7 @@ __global__ void __launch_bounds__(MT) k_resident(ResidentRun<T> a) {
         alpha = wave_uniform(rho / sigma);
         iter++;
 
+        keep();
         // ---- r -= alpha q, r* -= alpha q*; rho' = r*.r and r.r; x += alpha p
         Pair dt[2] = {{0.0, 0.0}, {0.0, 0.0}};
 #pragma unroll
@@ -560,6 +566,7 @@ __global__ void __launch_bounds__(MT) k_resident(ResidentRun<T> a) {
                 put_cell(xc, hdest[q], R[src], R[own + src]);
             }
         }
+        keep();
 #pragma unroll
         for (int c = 0; c < C; c++) {
             dot2_acc(dt[0], (double)s[c], (double)r[c]);
@@ -673,8 +680,8 @@ hipError_t launch_resident(const ResidentPlan &pl, ResidentRun<T> run, hipStream
 
 // Halo cells per thread and largest workgroup of the kernel with C cells per thread (what
 // its registers hold without spilling).
-constexpr int halo_slots(int C) { return C <= 2 ? 4 : C == 4 ? 6 : 8; }
-constexpr int max_threads(int C, bool fp64) { return C <= 2 && !fp64 ? 1024 : 512; }
+constexpr int halo_slots(int C) { return C <= 2 ? 4 : C == 4 ? 6 : C == 8 ? 8 : 11; }
+constexpr int max_threads(int C, bool fp64) { return C <= 2 && !fp64 ? 1024 : C == 16 && fp64 ? 0 : 512; }
 constexpr size_t kMaxLds = 158 * 1024;     // of 160 KB per workgroup; the rest is static
 
 bool try_plan(int n, bool fp64, int nbx, int nby, int nbz, int C, ResidentPlan &p) {
@@ -713,11 +720,14 @@ bool try_plan(int n, bool fp64, int nbx, int nby, int nbz, int C, ResidentPlan &
 // the best of each grid): work per wave and per thread, exchanges that grow with the number of
 // workgroups, cells exchanged.  Measured per iteration against the launch-per-sweep form:
 // 16^3 5.3 / 17.9, 32^3 5.4 / 18.3, 48^3 7.7 / 21.3, 64^3 10.0 / 26.1, 96^3 16.5 / 45.0 us.
-// Larger grids do not fit (above about 100^3), smaller ones are levels solved directly.
+// FP32 vectors: 96^3 37.3 -> 13.4 us, 112^3 48.9 -> 20.1, 128^3 (8192 cells per workgroup,
+// 16 per thread) 45 -> 22.  FP64 grids above about 100^3 do not fit (16 cells of six FP64
+// vectors and the halo take more than the 256 registers of 512 threads); smaller grids are
+// levels solved directly.
 bool resident_plan(int n, bool fp64, ResidentPlan &plan) {
     if (n < 7 || n > 128) return false;
     double best = 1e30;
-    for (int C : {1, 2, 4, 8})
+    for (int C : {1, 2, 4, 8, 16})
         for (int bz = 1; bz <= 16; bz++)
             for (int by = 1; by <= 16; by++)
                 for (int bx = 1; bx <= 8 && bx * by * bz <= kMaxGroups; bx++) {
@@ -749,6 +759,11 @@ hipError_t resident_run(const ResidentPlan &p, const ResidentRun<T> &run, hipStr
         EXCMG_RESIDENT(2)
         EXCMG_RESIDENT(4)
         EXCMG_RESIDENT(8)
+        case 16:
+            if constexpr (!f64)
+                return p.rs == 20 ? launch_resident<T, 16, 20, halo_slots(16), 512>(p, run, st)
+                                  : launch_resident<T, 16, 36, halo_slots(16), 512>(p, run, st);
+            return hipErrorInvalidValue;
         default: return hipErrorInvalidValue;
     }
 #undef EXCMG_RESIDENT

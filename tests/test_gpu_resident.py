@@ -48,7 +48,8 @@ def test_run_equals_oracle(ex, N, levels, bc):
     np.testing.assert_array_equal(x.cpu().numpy(), xr)
 
 
-@pytest.mark.parametrize("N,levels,bc", [(40, 4, 1), (64, 5, 2), (96, 6, 1), (96, 6, 2)])
+@pytest.mark.parametrize("N,levels,bc", [(40, 4, 1), (64, 5, 2), (96, 6, 1), (96, 6, 2),
+                                         (112, 5, 1), (128, 6, 2)])
 def test_mixed_cascade_equals_sweeps(ex, N, levels, bc):
     """FP32 vectors on every level, with residual replacements (resumed runs).  Timed sweeps
     take the launch-per-sweep form."""
