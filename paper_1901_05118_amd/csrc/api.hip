@@ -175,6 +175,20 @@ struct Ctx {
     DBuf res_cells, res_slots;
     unsigned res_epoch = 0;
     bool res_off = false;
+    // partition of each level per vector precision (FP64, FP32), made on first use (the search
+    // takes about as long as 100 iterations on a small grid); blocks == 0: none
+    struct LevelPlan {
+        bool made[2] = {false, false};
+        ResidentPlan plan[2];
+    };
+    LevelPlan res_plan[EXCMG_MAX_LEVELS];
+    const ResidentPlan &resident(const Level &L, bool fp64) {
+        LevelPlan &p = res_plan[L.index];
+        const int k = fp64 ? 0 : 1;
+        if (!p.made[k] && !resident_plan(L.n, dim, fp64, p.plan[k])) p.plan[k] = ResidentPlan{};
+        p.made[k] = true;
+        return p.plan[k];
+    }
     BicgState *host_state = nullptr;  // pinned; 3 slots (synchronous reads, pipelined polls)
     double *host_scal = nullptr;      // pinned
     hipEvent_t poll_ev[2] = {nullptr, nullptr};
@@ -195,6 +209,7 @@ struct Ctx {
         res_cells.release(); res_slots.release();
         res_epoch = 0;
         res_off = false;
+        for (LevelPlan &p : res_plan) p = LevelPlan{};
         if (host_state) (void)hipHostFree(host_state);
         for (hipEvent_t &e : poll_ev) {
             if (e) (void)hipEventDestroy(e);
@@ -708,7 +723,7 @@ int window_graph(const Level &L, TX *x, int K, hipGraphExec_t *out, int defer = 
     return EXCMG_OK;
 }
 
-// The whole run in one resident launch, on grids whose vectors fit on the chip (plain
+// The whole run in one resident launch, on grids and planes whose vectors fit on the chip (plain
 // Algorithm 2, contiguous rows, no explicit choice of the sweeps' form and no timing of
 // them).  *done = false: not taken (or given up, with nothing changed), and the
 // launch-per-sweep form runs.
@@ -716,11 +731,11 @@ template <typename T>
 int bicg_resident(const Level &L, double *x, BicgState &hs, bool *done) {
     Ctx &c = g_ctx;
     *done = false;
-    if (c.res_off || c.dim != 3 || g_cg || g_var.d || g_var.xs || g_timing || g_rq_min > 0 ||
+    if (c.res_off || g_cg || g_var.d || g_var.xs || g_timing || g_rq_min > 0 ||
         (sizeof(T) == 4 && L.ld != L.n) || hs.status != kRunning)
         return EXCMG_OK;
-    ResidentPlan plan;
-    if (!resident_plan(L.n, sizeof(T) == 8, plan)) return EXCMG_OK;
+    const ResidentPlan &plan = c.resident(L, sizeof(T) == 8);
+    if (plan.blocks == 0) return EXCMG_OK;
     const size_t cell_bytes = std::max((size_t)16, plan.exchange), slot_bytes = 6 * 256 * 16;
     const unsigned steps = (unsigned)std::max(0, hs.maxit - hs.iter) + 2;
     const bool wrap = c.res_epoch + steps < c.res_epoch;

@@ -217,7 +217,7 @@ hipError_t reduce_to(double *out, const Pair *part, int count, int slot, hipStre
 // A whole Bi-CG run in one cooperative launch (resident.hip): nbx x nby x nbz bricks of
 // bx x by x bz cells, one per workgroup, C consecutive z-cells per thread.
 struct ResidentPlan {
-    int nbx = 0, nby = 0, nbz = 0, bx = 0, by = 0, bz = 0, C = 0;
+    int nbx = 0, nby = 0, nbz = 0, bx = 0, by = 0, bz = 0, C = 0, dim = 3;
     int rs = 0;                    // row stride of the LDS box
     int threads = 0, blocks = 0;
     size_t lds = 0, exchange = 0;  // bytes of LDS; of exchanged cells
@@ -237,7 +237,7 @@ struct ResidentRun {
     void *slots;                   // exchanged partials: 6 planes of 16 bytes per workgroup (256)
     unsigned epoch;                // the run's exchanges are numbered from epoch + 1
 };
-bool resident_plan(int n, bool fp64, ResidentPlan &plan);
+bool resident_plan(int n, int dim, bool fp64, ResidentPlan &plan);
 template <typename T>
 hipError_t resident_run(const ResidentPlan &plan, const ResidentRun<T> &run, hipStream_t st);
 

@@ -4,7 +4,7 @@
 // What bounds the launch-per-sweep form there: two launches per iteration, each with its
 // drain, its dispatch and a merge of the other sweep's partials (9 us a launch on 16^3 and
 // 32^3), and from 64^3 on the vectors' way through the caches.  Here every workgroup owns a
-// brick of the grid for the whole run: the iterate and r, r*, p, p*, q, q* of its cells stay
+// brick of the grid (of the plane in 2D, the rows of which are z here) for the whole run: the iterate and r, r*, p, p*, q, q* of its cells stay
 // in registers, the marched array (p, then p*) in LDS with a 2-wide halo.  An iteration
 // exchanges, all past the L2 (which the XCDs do not share),
 //  * the partials of sigma, and of rho' and r.r (all to all: every workgroup merges all of
@@ -222,11 +222,54 @@ __device__ __forceinline__ void column_outputs(const T *B, int ps, Emit emit) {
     }
 }
 
+// The 13-point sums of the plane (2D): C consecutive rows of one column, B two cells and two
+// rows below output 0 (rows ps apart).  Terms in the order of plane2d.hpp.
+template <int C, typename T, class Emit>
+__device__ __forceinline__ void column_outputs_2d(const T *B, int ps, Emit emit) {
+    const T *P = B + 2 * ps;
+    double cm2 = B[2], cm1 = B[ps + 2], c0 = P[2], c1 = P[ps + 2];
+    double lm1 = B[ps + 1], rm1 = B[ps + 3], l0 = P[1], r0 = P[3];   // x-, x+ of rows k-1, k
+#pragma unroll
+    for (int k = 0; k < C; k++, P += ps) {
+        const double c2 = P[2 * ps + 2], l1 = P[ps + 1], r1 = P[ps + 3];
+        const double f0 = P[0], f1 = P[4];
+        const double s1 = l0 + r0 + cm1 + c1;
+        const double s2 = f0 + f1 + cm2 + c2;
+        const double s3 = lm1 + l1 + rm1 + r1;
+        emit(k, 20.0 * c0 - 8.0 * s1 + s2 + 2.0 * s3);
+        cm2 = cm1;
+        cm1 = c0;
+        c0 = c1;
+        c1 = c2;
+        lm1 = l0;
+        rm1 = r0;
+        l0 = l1;
+        r0 = r1;
+    }
+}
+
 // Halo cell h of a brick of bx x by x bz cells: its coordinates relative to the brick
-// (-2..b+1).  The scheme reaches two cells along an axis and one along two axes.
+// (-2..b+1).  The scheme reaches two cells along an axis and one along two axes.  In 2D the
+// plane's rows are z, and y is 0 (by = 1).
+template <int DIM>
 __device__ __forceinline__ bool halo_cell(int h, int bx, int by, int bz, int &x, int &y, int &z) {
     auto side = [](int s, int b) { return s < 2 ? s - 2 : b + s - 2; };   // -2, -1, b, b+1
     auto near = [](int s, int b) { return s == 0 ? -1 : b; };
+    if constexpr (DIM == 2) {
+        y = 0;
+        if (h < 4 * bx) {
+            x = h % bx; z = side(h / bx, bz);
+            return true;
+        }
+        h -= 4 * bx;
+        if (h < 4 * bz) {
+            x = side(h & 3, bx); z = h >> 2;
+            return true;
+        }
+        h -= 4 * bz;
+        x = near(h & 1, bx); z = near(h >> 1, bz);
+        return h < 4;
+    }
     if (h < 4 * bx * by) {
         x = h % bx; y = (h / bx) % by; z = side(h / (bx * by), bz);
         return true;
@@ -263,7 +306,7 @@ __device__ __forceinline__ bool halo_cell(int h, int bx, int by, int bz, int &x,
 
 // One run.  C: consecutive z-cells per thread; NH: halo cells per thread; MT: the largest
 // workgroup (threads); MULTI: more than one brick.
-template <typename T, int C, int RS, int NH, int MT, bool MULTI>
+template <int DIM, typename T, int C, int RS, int NH, int MT, bool MULTI>
 __global__ void __launch_bounds__(MT) k_resident(ResidentRun<T> a) {
     extern __shared__ char lds_raw[];
     __shared__ Pair red[2 * (MT / kWave)];
@@ -278,7 +321,9 @@ __global__ void __launch_bounds__(MT) k_resident(ResidentRun<T> a) {
               z0 = (blk / (a.nbx * a.nby)) * bz;
     const int groups = (bz + C - 1) / C;
     constexpr int BX = RS;
-    const int PS = BX * (by + 4), LE = PS * (groups * C + 4);
+    constexpr int HY = DIM == 3 ? 2 : 0;       // halo rows in y
+    const int ny = DIM == 3 ? n : 1;
+    const int PS = DIM == 3 ? BX * (by + 4) : BX, LE = PS * (groups * C + 4);
     BicgState *S = a.state;
     int status = S->status, iter = S->iter;
     if (status != kRunning) return;            // uniform
@@ -291,19 +336,19 @@ __global__ void __launch_bounds__(MT) k_resident(ResidentRun<T> a) {
     // this thread's column of C cells (those from `cells` on are none)
     const int lx = tid % bx, ly = (tid / bx) % by, lg = tid / (bx * by);
     const int gx = x0 + lx, gy = y0 + ly, gz = z0 + lg * C;
-    int cells = (lg < groups && gx < n && gy < n) ? max(0, min(C, min(n, z0 + bz) - gz)) : 0;
-    int ob = ((min(lg, groups - 1) * C + 2) * (by + 4) + ly + 2) * BX + lx + 2;
-    int gi = cells > 0 ? (gz * n + gy) * n + gx : 0;
-    const int gplane = cells > 0 ? n * n : 0;
+    int cells = (lg < groups && gx < n && gy < ny) ? max(0, min(C, min(n, z0 + bz) - gz)) : 0;
+    int ob = ((min(lg, groups - 1) * C + 2) * (by + 2 * HY) + ly + HY) * BX + lx + 2;
+    int gi = cells > 0 ? (gz * ny + gy) * n + gx : 0;
+    const int gplane = cells > 0 ? ny * n : 0;
     // fictitious points that mirror this column
     const int ghx = cells == 0 ? 0 : gx == 0 ? -2 : (gx == n - 1 ? 2 : 0);
-    const int ghy = cells == 0 ? 0 : gy == 0 ? -2 * BX : (gy == n - 1 ? 2 * BX : 0);
+    const int ghy = cells == 0 || DIM == 2 ? 0 : gy == 0 ? -2 * BX : (gy == n - 1 ? 2 * BX : 0);
     const int ghz0 = cells > 0 && gz == 0, ghz1 = cells > 0 && gz + cells == n;
     // Mailboxes: the halo cells of a brick, in the order of halo_cell, in one piece of memory.
     // This thread reads cells tid, tid + nt, ... of its own box, and sends the same cells of
     // its neighbours' boxes, as far as this brick owns them (bricks but the last of an axis
     // are whole, so cell h of a neighbour's box is owned by the brick on the other side).
-    const int hn = 4 * (bx * by + bx * bz + by * bz + bx + by + bz);
+    const int hn = DIM == 3 ? 4 * (bx * by + bx * bz + by * bz + bx + by + bz) : 4 * (bx + bz + 1);
     const __amdgpu_buffer_rsrc_t xc = exchange_rsrc(a.cells, 2u * sizeof(T) * (unsigned)(W * hn)),
                                  xs = exchange_rsrc(a.slots, 6 * kSlotPlane);
     const int own = bx * by * groups * C;     // staged r and r* of the brick: R, R + own
@@ -319,17 +364,17 @@ __global__ void __launch_bounds__(MT) k_resident(ResidentRun<T> a) {
             int x, y, z, place = LE;
             unsigned dest = kNoCell;
             const int h = tid + q * nt;
-            if (halo_cell(h, bx, by, bz, x, y, z)) {
+            if (halo_cell<DIM>(h, bx, by, bz, x, y, z)) {
                 const int X = x0 + x, Y = y0 + y, Z = z0 + z;
-                if (X >= 0 && X < n && Y >= 0 && Y < n && Z >= 0 && Z < n)
-                    place = ((z + 2) * (by + 4) + y + 2) * BX + x + 2;
+                if (X >= 0 && X < n && Y >= 0 && Y < ny && Z >= 0 && Z < n)
+                    place = ((z + 2) * (by + 2 * HY) + y + HY) * BX + x + 2;
                 // the brick that has cell h of its box here, and the cell's place in this one
                 const int dx = x < 0 ? 1 : (x >= bx ? -1 : 0), dy = y < 0 ? 1 : (y >= by ? -1 : 0),
                           dz = z < 0 ? 1 : (z >= bz ? -1 : 0);
                 const int X0 = x0 + dx * bx, Y0 = y0 + dy * by, Z0 = z0 + dz * bz;
                 const int sx = x + dx * bx, sy = y + dy * by, sz = z + dz * bz;
-                if (X0 >= 0 && X0 < n && Y0 >= 0 && Y0 < n && Z0 >= 0 && Z0 < n && x0 + sx < n &&
-                    y0 + sy < n && z0 + sz < n) {
+                if (X0 >= 0 && X0 < n && Y0 >= 0 && Y0 < ny && Z0 >= 0 && Z0 < n && x0 + sx < n &&
+                    y0 + sy < ny && z0 + sz < n) {
                     dest = (unsigned)((blk + dx + a.nbx * (dy + a.nby * dz)) * hn + h);
                     place |= ((sz * by + sy) * bx + sx) << 16;
                 }
@@ -410,8 +455,8 @@ __global__ void __launch_bounds__(MT) k_resident(ResidentRun<T> a) {
             for (int q = 0; q < NH; q++) {
                 hr[q] = hs[q] = hv[q] = (T)0;
                 int x, y, z;
-                if (hoff(q) != LE && halo_cell(tid + q * nt, bx, by, bz, x, y, z)) {
-                    const unsigned i = (unsigned)(((z0 + z) * n + y0 + y) * n + x0 + x);
+                if (hoff(q) != LE && halo_cell<DIM>(tid + q * nt, bx, by, bz, x, y, z)) {
+                    const unsigned i = (unsigned)(((z0 + z) * ny + y0 + y) * n + x0 + x);
                     hr[q] = a.r[i];
                     hs[q] = a.rs[i];
                     if (!first) {
@@ -435,6 +480,12 @@ __global__ void __launch_bounds__(MT) k_resident(ResidentRun<T> a) {
 #pragma unroll
             for (int q = 0; q < NH; q++) asm volatile("" : "+v"(hplace[q]), "+v"(hdest[q]));
         }
+    };
+
+    auto stencil = [&](auto emit) {
+        const T *B = M + (ob - 2 * PS - HY * RS - 2);
+        if constexpr (DIM == 3) column_outputs<C, RS, T>(B, PS, emit);
+        else column_outputs_2d<C, T>(B, PS, emit);
     };
 
     while (status == kRunning) {
@@ -472,7 +523,7 @@ __global__ void __launch_bounds__(MT) k_resident(ResidentRun<T> a) {
         // ---- q = A p, sigma = p*.q
         T qv[C], qs[C];
         Pair sg[1] = {{0.0, 0.0}};
-        column_outputs<C, RS, T>(M + (ob - 2 * PS - 2 * RS - 2), PS, [&](int c, double y) {
+        stencil([&](int c, double y) {
             qv[c] = c < cells ? (T)y : (T)0;
             dot2_acc(sg[0], (double)o[c], (double)qv[c]);
             // (one output after the other)
@@ -516,11 +567,10 @@ __global__ void __launch_bounds__(MT) k_resident(ResidentRun<T> a) {
         }
         __syncthreads();
         keep();
-        column_outputs<C, RS, T>(M + (ob - 2 * PS - 2 * RS - 2), PS,
-                                 [&](int c, double y) {
-                                     qs[c] = c < cells ? (T)y : (T)0;
-                                     if (C >= 8) asm volatile("" : "+v"(qs[c]));
-                                 });
+        stencil([&](int c, double y) {
+            qs[c] = c < cells ? (T)y : (T)0;
+            if (C >= 8) asm volatile("" : "+v"(qs[c]));
+        });
         // (q* is formed here, before the wait, not carried over it as its 21 C terms)
 #pragma unroll
         for (int c = 0; c < C; c++) asm volatile("" : "+v"(qs[c]));
@@ -667,10 +717,10 @@ __global__ void __launch_bounds__(MT) k_resident(ResidentRun<T> a) {
     }
 }
 
-template <typename T, int C, int RS, int NH, int MT>
+template <int DIM, typename T, int C, int RS, int NH, int MT>
 hipError_t launch_resident(const ResidentPlan &pl, ResidentRun<T> run, hipStream_t st) {
-    const void *fn = pl.blocks > 1 ? (const void *)k_resident<T, C, RS, NH, MT, true>
-                                   : (const void *)k_resident<T, C, RS, NH, MT, false>;
+    const void *fn = pl.blocks > 1 ? (const void *)k_resident<DIM, T, C, RS, NH, MT, true>
+                                   : (const void *)k_resident<DIM, T, C, RS, NH, MT, false>;
     hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)pl.lds);
     if (e != hipSuccess) return e;
     void *args[] = {&run};
@@ -679,35 +729,43 @@ hipError_t launch_resident(const ResidentPlan &pl, ResidentRun<T> run, hipStream
 }
 
 // Halo cells per thread and largest workgroup of the kernel with C cells per thread (what
-// its registers hold without spilling).
-constexpr int halo_slots(int C) { return C <= 2 ? 4 : C == 4 ? 6 : C == 8 ? 8 : 11; }
-constexpr int max_threads(int C, bool fp64) { return C <= 2 && !fp64 ? 1024 : C == 16 && fp64 ? 0 : 512; }
+// its registers hold without spilling; 16 cells: FP32 in 3D only).
+constexpr int halo_slots(int C, int dim) { return dim == 2 ? 2 : C <= 2 ? 4 : C == 4 ? 6 : C == 8 ? 8 : 11; }
+constexpr int max_threads(int C, bool fp64, int dim) {
+    return C == 16 && (fp64 || dim == 2) ? 0 : C <= 2 && !fp64 ? 1024 : 512;
+}
 constexpr size_t kMaxLds = 158 * 1024;     // of 160 KB per workgroup; the rest is static
 
-bool try_plan(int n, bool fp64, int nbx, int nby, int nbz, int C, ResidentPlan &p) {
+// Partition of the grid into nbx x nby x nbz bricks (2D: rows are z, nby = 1) with C cells
+// per thread; false if the kernels cannot take it.
+bool try_plan(int n, int dim, bool fp64, int nbx, int nby, int nbz, int C, ResidentPlan &p) {
+    const int ny = dim == 2 ? 1 : n;
     p.bx = (n + nbx - 1) / nbx;
-    p.by = (n + nby - 1) / nby;
+    p.by = (ny + nby - 1) / nby;
     p.bz = (n + nbz - 1) / nbz;
     p.nbx = (n + p.bx - 1) / p.bx;
-    p.nby = (n + p.by - 1) / p.by;
+    p.nby = (ny + p.by - 1) / p.by;
     p.nbz = (n + p.bz - 1) / p.bz;
     p.C = C;
+    p.dim = dim;
     p.blocks = p.nbx * p.nby * p.nbz;
     const bool one = p.blocks == 1;
     // rows of the LDS box hold up to 32 cells; a brick is at least as wide as the scheme reaches
-    if (p.blocks > kMaxGroups || p.bx > 32 || (!one && std::min({p.bx, p.by, p.bz}) < 2)) return false;
+    if (p.blocks > kMaxGroups || p.bx > 32) return false;
+    if (!one && (std::min(p.bx, p.bz) < 2 || (dim == 3 && p.by < 2))) return false;
     const int groups = (p.bz + C - 1) / C;
     const long long columns = (long long)p.bx * p.by * groups;
     // at least the four waves of merge_fixed, and two waves per 64 workgroups to gather the
     // partials of rho' and r.r
     const long long waves = std::max({4LL, (columns + 63) / 64, (p.blocks + 63) / 64 * 2LL});
-    if (64 * waves > max_threads(C, fp64)) return false;
+    if (64 * waves > max_threads(C, fp64, dim)) return false;
     p.threads = (int)(64 * waves);
-    const long long halo = 4LL * (p.bx * p.by + p.bx * p.bz + p.by * p.bz + p.bx + p.by + p.bz);
-    if (!one && halo > (long long)halo_slots(C) * p.threads) return false;
+    const long long halo = dim == 2 ? 4LL * (p.bx + p.bz + 1)
+                                    : 4LL * (p.bx * p.by + p.bx * p.bz + p.by * p.bz + p.bx + p.by + p.bz);
+    if (!one && halo > (long long)halo_slots(C, dim) * p.threads) return false;
     const size_t es = fp64 ? 8 : 4;
-    p.rs = p.bx <= 16 ? 20 : 36;
-    p.lds = ((size_t)p.rs * (p.by + 4) * (groups * C + 4) + 1) * es;
+    p.rs = p.bx <= 16 && dim == 3 ? 20 : 36;
+    p.lds = ((size_t)p.rs * (dim == 2 ? 1 : p.by + 4) * (groups * C + 4) + 1) * es;
     if (!one) p.lds += 2 * (size_t)columns * C * es;
     p.exchange = one ? 0 : (size_t)p.blocks * halo * 2 * es;
     return p.lds <= kMaxLds;
@@ -715,29 +773,33 @@ bool try_plan(int n, bool fp64, int nbx, int nby, int nbz, int C, ResidentPlan &
 
 }  // namespace
 
-// The partition of an n^3 grid: the cheapest by a model of an iteration's time (us), fitted to
-// some 5000 partitions of grids of 12 to 96 cells (FP64; what it picks takes 0-12% longer than
-// the best of each grid): work per wave and per thread, exchanges that grow with the number of
-// workgroups, cells exchanged.  Measured per iteration against the launch-per-sweep form:
-// 16^3 5.3 / 17.9, 32^3 5.4 / 18.3, 48^3 7.7 / 21.3, 64^3 10.0 / 26.1, 96^3 16.5 / 45.0 us.
-// FP32 vectors: 96^3 37.3 -> 13.4 us, 112^3 48.9 -> 20.1, 128^3 (8192 cells per workgroup,
-// 16 per thread) 45 -> 22.  FP64 grids above about 100^3 do not fit (16 cells of six FP64
-// vectors and the halo take more than the 256 registers of 512 threads); smaller grids are
+// The partition of an n^3 grid or n^2 plane: the cheapest by a model of an iteration's time
+// (us), fitted to some 5000 partitions of 3D grids of 12 to 96 cells (FP64; what it picks takes
+// 0-12% longer than the best of each grid): work per wave and per thread, exchanges that grow
+// with the number of workgroups, cells exchanged.  Measured per iteration against the
+// launch-per-sweep form: 16^3 5.3 / 17.9, 32^3 5.4 / 18.3, 48^3 7.7 / 21.3, 64^3 10.0 / 26.1,
+// 96^3 16.5 / 45.0 us.  FP32 vectors: 96^3 13.4 / 37.3, 112^3 20.1 / 48.9, 128^3 (8192 cells
+// per workgroup, 16 per thread) 22 / 45.  Planes, FP64: 128^2 4.7 / 12.1, 256^2 5.0 / 13.3,
+// 512^2 7.3 / 24.2, 1024^2 (whole run of 15) 24 / 64.
+// FP64 grids above about 100^3 do not fit (16 cells of six FP64 vectors and the halo take more
+// than the 256 registers of 512 threads), nor do planes above about 1000^2; smaller grids are
 // levels solved directly.
-bool resident_plan(int n, bool fp64, ResidentPlan &plan) {
-    if (n < 7 || n > 128) return false;
+bool resident_plan(int n, int dim, bool fp64, ResidentPlan &plan) {
+    if (n < 7 || n > (dim == 2 ? 1024 : 128)) return false;
     double best = 1e30;
+    const int most = dim == 2 ? kMaxGroups : 16;
     for (int C : {1, 2, 4, 8, 16})
-        for (int bz = 1; bz <= 16; bz++)
-            for (int by = 1; by <= 16; by++)
-                for (int bx = 1; bx <= 8 && bx * by * bz <= kMaxGroups; bx++) {
+        for (int bz = 1; bz <= most; bz++)
+            for (int by = 1; by <= (dim == 2 ? 1 : most); by++)
+                for (int bx = 1; bx <= (dim == 2 ? 32 : 8) && bx * by * bz <= kMaxGroups; bx++) {
                     ResidentPlan p;
-                    if (!try_plan(n, fp64, bx, by, bz, C, p)) continue;
+                    if (!try_plan(n, dim, fp64, bx, by, bz, C, p)) continue;
                     const double waves = p.threads / 64, W = p.blocks;
                     double t = 0.056 * waves * C + 0.086 * waves + 0.36 * C;
                     if (p.blocks > 1)
                         t += 0.83 + 0.094 * W / 64 + 0.32 * ((p.blocks + 63) / 64) +
-                             0.048 * waves * halo_slots(C) + 2.1e-7 * (double)p.exchange * (fp64 ? 1 : 2);
+                             0.048 * waves * halo_slots(C, dim) +
+                             2.1e-7 * (double)p.exchange * (fp64 ? 1 : 2);
                     if (t < best) {
                         best = t;
                         plan = p;
@@ -746,24 +808,29 @@ bool resident_plan(int n, bool fp64, ResidentPlan &plan) {
     return best < 1e30;
 }
 
+template <int DIM, typename T, int C>
+hipError_t run_cells(const ResidentPlan &p, const ResidentRun<T> &run, hipStream_t st) {
+    constexpr int MT = max_threads(C, sizeof(T) == 8, DIM), NH = halo_slots(C, DIM);
+    if constexpr (MT == 0) {
+        return hipErrorInvalidValue;
+    } else {
+        if constexpr (DIM == 3) {
+            if (p.rs == 20) return launch_resident<DIM, T, C, 20, NH, MT>(p, run, st);
+        }
+        return launch_resident<DIM, T, C, 36, NH, MT>(p, run, st);
+    }
+}
+
 template <typename T>
 hipError_t resident_run(const ResidentPlan &p, const ResidentRun<T> &run, hipStream_t st) {
-    constexpr bool f64 = sizeof(T) == 8;
-#define EXCMG_RESIDENT(CV)                                                                  \
-    case CV:                                                                                \
-        return p.rs == 20                                                                   \
-                   ? launch_resident<T, CV, 20, halo_slots(CV), max_threads(CV, f64)>(p, run, st)  \
-                   : launch_resident<T, CV, 36, halo_slots(CV), max_threads(CV, f64)>(p, run, st);
+#define EXCMG_RESIDENT(CV) \
+    case CV: return p.dim == 2 ? run_cells<2, T, CV>(p, run, st) : run_cells<3, T, CV>(p, run, st);
     switch (p.C) {
         EXCMG_RESIDENT(1)
         EXCMG_RESIDENT(2)
         EXCMG_RESIDENT(4)
         EXCMG_RESIDENT(8)
-        case 16:
-            if constexpr (!f64)
-                return p.rs == 20 ? launch_resident<T, 16, 20, halo_slots(16), 512>(p, run, st)
-                                  : launch_resident<T, 16, 36, halo_slots(16), 512>(p, run, st);
-            return hipErrorInvalidValue;
+        EXCMG_RESIDENT(16)
         default: return hipErrorInvalidValue;
     }
 #undef EXCMG_RESIDENT

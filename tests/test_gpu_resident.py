@@ -9,6 +9,7 @@ import pytest
 
 import oracle as O
 from manufactured import config_problem, make_arrays
+from manufactured.twod import family_2d, make_arrays_2d
 
 pytestmark = pytest.mark.gpu
 
@@ -62,6 +63,45 @@ def test_mixed_cascade_equals_sweeps(ex, N, levels, bc):
         ex.set_timing(timed)
         rc, st = ex.solve_ex(N, levels, bc, f, g1, g2, 1e-7, u, precision=ex.MIXED,
                              fp32_min_unknowns=1)
+        assert rc == ex.OK, ex.last_error()
+        launches = ex.get_timing(levels - 1, 0)[1] + ex.get_timing(levels - 1, 2)[1]
+        assert (launches > 0) == timed
+        got.append((u.cpu().numpy(), [(s["iterations"], s["runs"]) for s in st.levels()]))
+    ex.set_timing(False)
+    assert got[0][1] == got[1][1]
+    np.testing.assert_array_equal(got[0][0], got[1][0])
+
+
+# planes: one brick (8, 24), whole and partial rows of bricks, one to eight cells per thread;
+# 1024^2 is the largest plane the form takes
+@pytest.mark.parametrize("N,levels", [(8, 3), (24, 3), (40, 4), (64, 5), (96, 5), (200, 4), (256, 7),
+                                      (512, 6), (1024, 6)])
+@pytest.mark.parametrize("bc", [1, 2])
+def test_plane_run_equals_oracle(ex, N, levels, bc):
+    print(f"resident plane N={N} bc={bc}", flush=True)
+    ex.setup_2d(N, levels, bc)
+    rng = np.random.default_rng(N + bc)
+    b, x0 = rng.standard_normal((2, (N - 1) ** 2))
+    its = 12
+    x = dev(x0)
+    rc, it, rr = ex.bicg(levels - 1, dev(b), x, 0.0, its)
+    xr, itr, rrr, rcr = O.bicg_2d(N, bc, b, x0, 0.0, maxit=its)
+    assert rc == ex.ENOCONV and it == itr == its
+    assert rr == rrr
+    np.testing.assert_array_equal(x.cpu().numpy(), xr)
+
+
+@pytest.mark.parametrize("N,levels,bc", [(96, 5, 1), (512, 6, 1), (512, 6, 2), (1024, 6, 1)])
+def test_mixed_plane_equals_sweeps(ex, N, levels, bc):
+    print(f"resident mixed plane N={N} bc={bc}", flush=True)
+    arr = make_arrays_2d(family_2d(5), N, bc)
+    f, g1, g2 = dev(arr.f), dev(arr.g1), dev(arr.g2)
+    got = []
+    for timed in (False, True):
+        u = torch.empty_like(f)
+        ex.set_timing(timed)
+        rc, st = ex.solve_ex_2d(N, levels, bc, f, g1, g2, 1e-9, u, precision=ex.MIXED,
+                                fp32_min_unknowns=1)
         assert rc == ex.OK, ex.last_error()
         launches = ex.get_timing(levels - 1, 0)[1] + ex.get_timing(levels - 1, 2)[1]
         assert (launches > 0) == timed
