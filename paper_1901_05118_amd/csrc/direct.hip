@@ -107,92 +107,192 @@ __global__ void __launch_bounds__(1024) k_band_cholesky(int n, int w, double *C,
 
 constexpr int kBandMaxN = 4096;
 
-// L y = b, then L^T x = y, in one wavefront with the vector in LDS (b and x may alias).
-// Forward: column k is applied to the rows below it in parallel.  Backward: row i needs
-// x_{i+1} before its first subtraction, so the chain itself is serial; the lanes form the
-// products L(k,i) x_k in parallel and one lane subtracts them in ascending k.  Either way
-// a step is short next to the latency of a column's load, so the columns come in chunks of
-// DP: while the steps of one chunk run, the next chunk's loads are in flight (waited for
-// once, at the end of the chunk).  Entry e = lane + 64 q of a column (e = 0 the diagonal,
-// which lane 0 broadcasts) is loaded unconditionally from an index clamped into the
-// column's w+1 stored entries; the steps mask what lies past the column's last row.
-template <int PER, int DP>
+// a / d from y = 1/d (correctly rounded; 0: not usable) by two corrections of a y: the second
+// starts from a quotient within one unit of the last place, with an exact remainder, so it
+// gives the correctly rounded one (P. Markstein, IBM J. Res. Dev. 34, 1990).  Five dependent
+// operations instead of the dozen of a general division.  Quotients that come near the ends
+// of the exponent range, zeros, infinities and NaN take the general one.  a is the same in
+// all lanes.
+__device__ __forceinline__ double quotient(double a, double d, double y) {
+    double q = a * y;
+    q = fma(fma(-q, d, a), y, q);
+    q = fma(fma(-q, d, a), y, q);
+    const int e = (__builtin_amdgcn_readfirstlane(__double2hiint(a)) >> 20) & 2047;
+    const int outside = (int)((unsigned)(e - 256) >= 1536u) |
+                        (int)(__builtin_amdgcn_readfirstlane(__double2hiint(y)) == 0);
+    if (__builtin_expect(outside, 0)) q = a / d;
+    return q;
+}
+__device__ __forceinline__ double reciprocal(double d) {
+    return d >= 0x1p-100 && d <= 0x1p100 ? 1.0 / d : 0.0;
+}
+__device__ __forceinline__ double lane_value(double v, int lane) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                            __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+// Orders LDS accesses of one wavefront (which the LDS takes in program order).
+__device__ __forceinline__ void wave_order() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// L y = b, then L^T x = y, in one wavefront (b and x may alias).
+//
+// What bounds it: a serial chain.  Forward, y_k = t_k / L(k,k) must be there before y_k+1 can
+// be formed; backward, row i subtracts its w products in ascending k starting with the one
+// that needs x_{i+1}, so the whole solve is n w dependent subtractions.
+//
+// Forward: the rows of a block of 64 and those its columns reach are in registers, row
+// 64 (block + q) + lane in slot q; a step broadcasts its pivot row's value by a lane read.
+// Backward: the chain runs in every lane alike on products read from LDS, 16 ahead.  The
+// products of the next row (all but the first, which needs x_i) are formed by the lanes
+// meanwhile; what lies past a column's last row is +0, which changes no difference.  The
+// diagonal's reciprocals are formed for 64 rows at once.  The columns come in chunks of DP:
+// while the steps of one run, the next one's loads are in flight.
+// Per row at w = 126 (64^2): forward 460 cycles (readlane, quotient, update), backward 1550, 9
+// a subtraction: reading a product pair costs the wave about as much as its two additions
+// (5.3 each).  Against a step with LDS round trips forward, and products formed and waited
+// for before each row's chain by one lane: 64^2 6.8 -> 3.3 ms, 32^2 1.02 -> 0.55, 16^3
+// 15.7 -> 8.4, 8^3 0.45 -> 0.30.
+template <int PER, int NG, int DP>
 __global__ void __launch_bounds__(64) k_band_solve(int n, int w, const double *C, const double *b,
                                                    double *x) {
+    constexpr int S = PER + 1;          // slots of 64 rows that a block's columns reach
+    constexpr int PROD = 64 * PER + 32;  // >= 16 NG
+    static_assert(NG % 2 == 0 && PER == (NG + 3) / 4);
     __shared__ double t[kBandMaxN];
-    __shared__ double prod[64 * PER];
+    __shared__ __align__(16) double prod[2][PROD];
     const int lane = threadIdx.x;
     const i64 ld = (i64)w + 1;
-    for (int i = lane; i < n; i += 64) t[i] = b[i];
-    __syncthreads();
+    for (int i = lane; i < 2 * PROD; i += 64) prod[0][i] = 0.0;
 
-    auto load_col = [&](int k, double (&v)[PER]) {
-        const double *col = C + (i64)k * ld;
+    // forward
+    {
+        double v[S], cur[DP][S], nxt[DP][S];
+        auto load_rows = [&](int row) { return row < n ? b[row] : 0.0; };
+        auto load_col = [&](int k, double (&c)[S]) {
+            const double *col = C + (i64)min(k, n - 1) * ld;
 #pragma unroll
-        for (int q = 0; q < PER; q++) v[q] = col[min(lane + 64 * q, w)];
-    };
-    double cur[DP][PER], nxt[DP][PER];
+            for (int q = 0; q < S; q++) c[q] = col[(unsigned)min(max(64 * q + lane - (k & 63), 0), w)];
+        };
 #pragma unroll
-    for (int s = 0; s < DP; s++)
+        for (int q = 0; q < S; q++) v[q] = load_rows(64 * q + lane);
+        double diag = C[(i64)min(lane, n - 1) * ld];
 #pragma unroll
-        for (int q = 0; q < PER; q++) cur[s][q] = nxt[s][q] = 0.0;
-    auto swap_in = [&]() {
+        for (int s = 0; s < DP; s++) load_col(s, cur[s]);
+        for (int k0 = 0; k0 < n; k0 += 64) {
+            const double inv = reciprocal(diag);
+            const double next_diag = C[(i64)min(k0 + 64 + lane, n - 1) * ld];
+            const double next_rows = load_rows(k0 + 64 * S + lane);
+#pragma unroll 1
+            for (int s0 = 0; s0 < min(64, n - k0); s0 += DP) {
+                // unconditional (clamped) requests, so the loads in flight are counted exactly
 #pragma unroll
-        for (int s = 0; s < DP; s++)
+                for (int s = 0; s < DP; s++) load_col(k0 + s0 + DP + s, nxt[s]);
 #pragma unroll
-            for (int q = 0; q < PER; q++) cur[s][q] = nxt[s][q];
-    };
-
+                for (int s = 0; s < DP; s++) {
+                    const int l = s0 + s;
+                    __builtin_amdgcn_sched_barrier(0);
+                    const double yk = quotient(lane_value(v[0], l), lane_value(diag, l),
+                                               lane_value(inv, l));
 #pragma unroll
-    for (int s = 0; s < DP; s++) load_col(min(s, n - 1), cur[s]);
-    for (int k0 = 0; k0 < n; k0 += DP) {
-        // unconditional (clamped) requests, so the loads in flight are counted exactly
-#pragma unroll
-        for (int s = 0; s < DP; s++) load_col(min(k0 + DP + s, n - 1), nxt[s]);
-#pragma unroll
-        for (int s = 0; s < DP; s++) {
-            const int k = k0 + s;
-            if (k < n) {
-                const int m = min(w, n - 1 - k);
-                const double yk = t[k] / __shfl(cur[s][0], 0);
-#pragma unroll
-                for (int q = 0; q < PER; q++) {
-                    const int e = lane + 64 * q;
-                    if (e >= 1 && e <= m) t[k + e] -= cur[s][q] * yk;
+                    for (int q = 0; q < S; q++) {
+                        const int e = 64 * q + lane - l;
+                        const double u = v[q] - cur[s][q] * yk;
+                        if (q == 0) v[q] = e >= 1 && e <= w ? u : (e == 0 ? yk : v[q]);
+                        else v[q] = e <= w ? u : v[q];
+                    }
                 }
-                if (lane == 0) t[k] = yk;
-                __syncthreads();
+#pragma unroll
+                for (int s = 0; s < DP; s++)
+#pragma unroll
+                    for (int q = 0; q < S; q++) cur[s][q] = nxt[s][q];
             }
+            t[k0 + lane] = k0 + lane < n ? v[0] : 0.0;
+#pragma unroll
+            for (int q = 0; q + 1 < S; q++) v[q] = v[q + 1];
+            v[S - 1] = next_rows;
+            diag = next_diag;
         }
-        swap_in();
+        wave_order();
     }
 
+    // backward
+    {
+        double cur[DP][PER], nxt[DP][PER];
+        const int k1 = (n - 1) & ~63;
+        auto load_col = [&](int k, double (&c)[PER]) {
+            const double *col = C + (i64)min(max(k, 0), n - 1) * ld;
 #pragma unroll
-    for (int s = 0; s < DP; s++) load_col(max(n - 1 - s, 0), cur[s]);
-    for (int k0 = 0; k0 < n; k0 += DP) {
+            for (int q = 0; q < PER; q++) c[q] = col[(unsigned)min(lane + 64 * q, w)];
+        };
+        // the rows past the last one of its chunk are zeros (t holds zeros there)
+        int s0 = (63 - (n - 1 - k1)) / DP * DP;
+        double xi = 0.0, ti = t[k1 + 63 - s0];
+        double first[16], second[16];     // products: of the row at hand, 16 ahead of the chain
 #pragma unroll
-        for (int s = 0; s < DP; s++) load_col(max(n - 1 - (k0 + DP + s), 0), nxt[s]);
+        for (int e = 0; e < 16; e++) first[e] = 0.0;
+        double diag = C[(i64)min(k1 + lane, n - 1) * ld];
 #pragma unroll
-        for (int s = 0; s < DP; s++) {
-            const int i = n - 1 - (k0 + s);
-            if (i >= 0) {
-                const int m = min(w, n - 1 - i);
+        for (int s = 0; s < DP; s++) load_col(k1 + 63 - s0 - s, cur[s]);
+        for (int k0 = k1; k0 >= 0; k0 -= 64) {
+            const double inv = reciprocal(diag);
+            const double next_diag = C[(i64)max(k0 - 64 + lane, 0) * ld];
+#pragma unroll 1
+            for (; s0 < 64; s0 += DP) {
 #pragma unroll
-                for (int q = 0; q < PER; q++) {
-                    const int e = lane + 64 * q;
-                    if (e >= 1 && e <= m) prod[e - 1] = cur[s][q] * t[i + e];
+                for (int s = 0; s < DP; s++) load_col(k0 + 63 - (s0 + DP + s), nxt[s]);
+#pragma unroll
+                for (int s = 0; s < DP; s++) {
+                    const int l = 63 - (s0 + s), i = k0 + l;
+                    __builtin_amdgcn_sched_barrier(0);
+                    const double *P = prod[i & 1];
+                    double *Q = prod[(i & 1) ^ 1];
+                    double tv[PER];
+#pragma unroll
+                    for (int q = 0; q < PER; q++) tv[q] = t[min(max(i - 1 + lane + 64 * q, 0), n - 1)];
+                    const double t_next = t[max(i - 1, 0)];
+#pragma unroll
+                    for (int e = 0; e < 16; e++) second[e] = P[16 + e];
+                    __builtin_amdgcn_sched_barrier(0);
+                    double acc = ti - lane_value(cur[s][0], 1) * xi;
+#pragma unroll
+                    for (int e = 0; e < 16; e++) acc -= first[e];
+                    // the next row's products from its third entry on
+                    const int m = min(w, n - i);
+#pragma unroll
+                    for (int q = 0; q < PER; q++) {
+                        const int e = lane + 64 * q;
+                        const double c = s + 1 < DP ? cur[s + 1 < DP ? s + 1 : 0][q] : nxt[0][q];
+                        if (e >= 2) Q[e - 2] = e <= m ? c * tv[q] : 0.0;
+                    }
+                    wave_order();
+#pragma unroll
+                    for (int g = 1; g < NG; g++) {
+                        double (&now)[16] = (g & 1) ? second : first;
+                        double (&then)[16] = (g & 1) ? first : second;
+                        const double *F = g + 1 < NG ? P + 16 * (g + 1) : Q;
+#pragma unroll
+                        for (int e = 0; e < 16; e++) then[e] = F[e];
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int e = 0; e < 16; e++) acc -= now[e];
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    xi = quotient(acc, lane_value(diag, l), lane_value(inv, l));
+                    t[i] = xi;
+                    ti = t_next;
+                    wave_order();
                 }
-                const double d = __shfl(cur[s][0], 0);
-                __syncthreads();
-                if (lane == 0) {
-                    double acc = t[i];
-                    for (int e = 0; e < m; e++) acc -= prod[e];
-                    t[i] = acc / d;
-                }
-                __syncthreads();
+#pragma unroll
+                for (int s = 0; s < DP; s++)
+#pragma unroll
+                    for (int q = 0; q < PER; q++) cur[s][q] = nxt[s][q];
             }
+            s0 = 0;
+            diag = next_diag;
         }
-        swap_in();
     }
     for (int i = lane; i < n; i += 64) x[i] = t[i];
 }
@@ -222,16 +322,24 @@ hipError_t band_cholesky(int n, int w, double *C, int *info, hipStream_t st) {
 
 hipError_t band_solve(int n, int w, const double *C, const double *b, double *x, hipStream_t st) {
     if (n < 1 || n > kBandMaxN || w < 0 || w + 1 > 64 * 8) return hipErrorInvalidValue;
-    const int per = (w + 64) / 64;   // the w+1 entries of a column (diagonal included)
-    if (per <= 1)
-        hipLaunchKernelGGL((k_band_solve<1, 8>), dim3(1), dim3(64), 0, st, n, w, C, b, x);
-    else if (per <= 2)
-        hipLaunchKernelGGL((k_band_solve<2, 8>), dim3(1), dim3(64), 0, st, n, w, C, b, x);
-    else if (per <= 4)
-        hipLaunchKernelGGL((k_band_solve<4, 4>), dim3(1), dim3(64), 0, st, n, w, C, b, x);
-    else
-        hipLaunchKernelGGL((k_band_solve<8, 4>), dim3(1), dim3(64), 0, st, n, w, C, b, x);
-    return hipGetLastError();
+    // 16 NG >= w-1 products of a row and 64 PER >= w+1 entries of a column, PER = ceil(NG / 4)
+#define EXCMG_SOLVE(NG, DP)                                                                     \
+    if (w - 1 <= 16 * NG && w + 1 <= (NG + 3) / 4 * 64) {                                       \
+        hipLaunchKernelGGL((k_band_solve<(NG + 3) / 4, NG, DP>), dim3(1), dim3(64), 0, st, n, w, C, b, x); \
+        return hipGetLastError();                                                               \
+    }
+    EXCMG_SOLVE(2, 8)
+    EXCMG_SOLVE(4, 8)
+    EXCMG_SOLVE(6, 8)
+    EXCMG_SOLVE(8, 8)
+    EXCMG_SOLVE(12, 4)
+    EXCMG_SOLVE(16, 4)
+    EXCMG_SOLVE(20, 4)
+    EXCMG_SOLVE(24, 4)
+    EXCMG_SOLVE(28, 4)
+    EXCMG_SOLVE(32, 4)
+#undef EXCMG_SOLVE
+    return hipErrorInvalidValue;
 }
 
 }  // namespace excmg

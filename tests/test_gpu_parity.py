@@ -728,3 +728,20 @@ def _cg_oracle(N, nl, bc, c):
         arr = make_arrays(config_problem(c), N, bc)
         _CG_ORACLE[key] = O.excmg(N, nl, bc, arr.f, arr.g1, arr.g2, 1e-9)
     return _CG_ORACLE[key]
+
+
+# (dim, coarsest cells): bandwidths on both sides of 32, 64, 128 and 256 entries and the widest
+# band; unknowns that end a block of 64 rows and that do not
+@pytest.mark.parametrize("dim,N0", [(2, 2), (2, 9), (2, 17), (2, 18), (2, 25), (2, 32), (3, 5),
+                                    (3, 6), (3, 7), (3, 8)])
+def test_dsolve_over_the_bandwidths(ex, dim, N0):
+    (ex.setup if dim == 3 else ex.setup_2d)(N0 * 4, 3, 1)
+    solve = O.dsolve if dim == 3 else O.dsolve_2d
+    for level in (0, 1):
+        N = N0 << level
+        b = np.random.default_rng(N).standard_normal((N - 1) ** dim)
+        # the second right-hand side has zeros, and quotients near the ends of the range
+        for scale in (np.ones_like(b), np.where(np.arange(b.size) % 5 == 0, 0.0, 2.0 ** -1015)):
+            x = torch.empty_like(dev(b))
+            ex.dsolve(level, dev(b * scale), x)
+            np.testing.assert_array_equal(host(x), solve(N, 1, b * scale))
