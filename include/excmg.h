@@ -92,8 +92,10 @@ typedef struct excmg_opts {
                         /* (0: 0.1 with EXCMG_RELIABLE, 1e-4 with EXCMG_RESTART, 1e-5 with  */
                         /* EXCMG_RESTART in excmg_solve_batch)                              */
     int max_outer;      /* mixed precision: refinement steps per level (0: 60)             */
-    int batch_mode;     /* excmg_solve_batch: 0 = four graph-captured phase launches per    */
-                        /* Bi-CG step, 1 = one persistent work-queue launch per step        */
+    int batch_mode;     /* excmg_solve_batch: 0 = runs of whole systems in shared launches  */
+                        /* where they fit on the chip, else four graph-captured phase       */
+                        /* launches per Bi-CG step, 1 = one persistent work-queue launch    */
+                        /* per step                                                         */
     int method;         /* EXCMG_BICG (default) or EXCMG_CG (excmg_solve_ex only)           */
     int refine;         /* mixed precision: EXCMG_RELIABLE (default) or EXCMG_RESTART      */
     int precond;        /* EXCMG_PRECOND_NONE (default) or EXCMG_PRECOND_JACOBI (solve_ex) */
@@ -333,13 +335,15 @@ typedef struct excmg_problem {
 } excmg_problem;
 
 /* Algorithm 1 for nprob independent problems (1..256) of possibly different grids, levels
- * and boundary kinds, advanced together: one Bi-CG iteration of all running systems is four
- * phase launches (opts.batch_mode 0) or one launch of a persistent work-queue kernel
- * (batch_mode 1), replayed in windows from captured hipGraphs, while each problem follows
- * its own cascade, tolerances and stopping decisions exactly as excmg_solve_ex would.
+ * and boundary kinds, advanced together.  opts.batch_mode 0: levels whose Bi-CG vectors fit on
+ * the chip (FP64 up to about 100^3, FP32 up to 128^3) run resident, several systems in one
+ * cooperative launch; one Bi-CG iteration of all other running systems is four phase launches.
+ * batch_mode 1: one launch of a persistent work-queue kernel per iteration of all systems.
+ * Steps are replayed in windows from captured hipGraphs.  Each problem follows its own cascade,
+ * tolerances and stopping decisions exactly as excmg_solve_ex would.
  * Mixed precision: levels of at least opts.fp32_min_unknowns unknowns (0: 2^18) run FP32
  * Bi-CG inside FP64 refinement; smaller levels run FP64 Bi-CG, as in an FP64 solve (systems
- * of the two kinds advance in separate launches on two streams).  opts.refine: with
+ * of the two kinds advance by steps in separate launches on two streams).  opts.refine: with
  * EXCMG_RELIABLE (default) a run stops when its recurrence residual has fallen by
  * inner_tol (0: 0.1) or below half the level's target, the FP64 residual replaces r and r*
  * and the run goes on with its search directions; with EXCMG_RESTART each refinement step

@@ -1422,6 +1422,8 @@ struct BProb {
     int runs = 0, iters = 0, outer = 0, worst = EXCMG_OK;
     int iter_base = 0;          // the run's iteration count when it was last (re)started
     int broke = 0;              // the last run broke down (Algorithm 2's denominators)
+    bool resident = false;      // the run is advanced by the resident launch, not by steps
+    int iter_now = 0;           // the run's iteration count when its state was last read
     double eps = 0.0, prev = INFINITY, last_bb = 0.0;
     double level_bb[EXCMG_MAX_LEVELS] = {};   // b.b of each finished level
     excmg_stats stats{};
@@ -1459,6 +1461,34 @@ struct StepSet {
     }
 };
 
+// The running systems of a batch whose vectors fit on the chip, as many of them at a time as
+// there are CUs for, in one resident launch (resident.hip).
+struct ResidentSet {
+    struct Plans {
+        int n;
+        bool fp64;
+        ResidentPlan share[kBatchShares];
+    };
+    std::vector<Plans> plans;      // of the grids met so far
+    DBuf table, cells, slots, flags;
+    ResidentBatchRun *h_table = nullptr;
+    unsigned epoch = 0;
+    bool off = false;              // (a wait ran out, or no room: the steps take all systems)
+    std::vector<int> now;          // systems of the launch in flight
+    ~ResidentSet() {
+        table.release(); cells.release(); slots.release(); flags.release();
+        if (h_table) (void)hipHostFree(h_table);
+    }
+    const Plans &of(int n, bool fp64) {
+        for (const Plans &p : plans)
+            if (p.n == n && p.fp64 == fp64) return p;
+        Plans p{n, fp64, {}};
+        resident_batch_plans(n, fp64, p.share);
+        plans.push_back(p);
+        return plans.back();
+    }
+};
+
 struct BatchSolver {
     bool mixed = false;
     bool reliable = true;     // FP32 levels: residual replacement (else restarted refinement)
@@ -1475,12 +1505,13 @@ struct BatchSolver {
     double *h_scal = nullptr;
     BicgState *h_states = nullptr;
     StepSet set[2];           // systems with FP64 vectors, with FP32 vectors
+    ResidentSet res;
     // while both kinds run, the FP32 systems' steps go to a second stream (forked from and
     // joined to st by events) and run beside the FP64 systems' steps
     hipStream_t st2 = nullptr;
     hipEvent_t fork = nullptr, join = nullptr;
     // Bi-CG steps per captured graph between two reads of the states (64 problems of
-    // 32^3-128^3, one box: 4 / 8 / 16 steps, FP64 1279 / 1252 / 1237 ms, mixed 1180 / 1128 /
+    // 32^3-128^3, all by steps, one machine: 4 / 8 / 16 steps, FP64 1279 / 1252 / 1237 ms, mixed 1180 / 1128 /
     // 1112 ms; another: 16 / 32 steps, FP64 1240 / 1233 ms, mixed 1117 / 1102 ms)
     int steps_per_graph = 32;
     long long launches = 0;
@@ -1517,6 +1548,7 @@ struct BatchSolver {
         CKR(states.ensure((size_t)nprob * sizeof(BicgState)));
         CKR(runs.ensure((size_t)nprob * sizeof(BatchRun)));
         CKR(scal.ensure((size_t)nprob * 4 * sizeof(double)));
+        CKH(hipMemsetAsync(states.p, 0, (size_t)nprob * sizeof(BicgState), st));
         const int one = 1;
         for (int k = 0; k < 2; k++) {
             StepSet &S = set[k];
@@ -1696,7 +1728,7 @@ struct BatchSolver {
             if (b.runs >= max_runs) return finish_level(j, EXCMG_ENOCONV, rr, bb);
             CKH((copy_convert<double, double>(Lv.nu, b.r.as<double>(), b.rs.as<double>(), st)));
             CKH(bicg_start(Sj, b.part_a.as<Pair>(), stencil_blocks(Lv.g1), b.eps, maxit, st));
-            b.iter_base = 0;
+            b.iter_base = b.iter_now = 0;
         } else {
             if (b.outer >= max_outer || !(rr < b.prev)) return finish_level(j, EXCMG_ENOCONV, rr, bb);
             // a run of this level stopped at its threshold: with residual replacement it goes
@@ -1712,18 +1744,18 @@ struct BatchSolver {
                 const double rthr = std::max((inner_tol * inner_tol) * rr, 0.25 * thr);
                 if (resume) {
                     CKH(batch_resume(Sj, b.part_b.as<Pair>(), nvb, rthr, st));
-                    b.iter_base = h_states[j].iter;
+                    b.iter_base = b.iter_now = h_states[j].iter;
                 } else {
                     CKH(reduce_to((double *)&Sj->bb, b.part_b.as<Pair>(), nvb, 0, st));
                     CKH(bicg_start(Sj, b.part_b.as<Pair>(), nvb, std::sqrt(rthr / rr), maxit, st));
-                    b.iter_base = 0;
+                    b.iter_base = b.iter_now = 0;
                 }
             } else {
                 double it = std::max(inner_tol, 0.3 * b.eps * std::sqrt(bb / rr));
                 if (it > 0.5) it = 0.5;
                 CKH(reduce_to((double *)&Sj->bb, b.part_b.as<Pair>(), nvb, 0, st));
                 CKH(bicg_start(Sj, b.part_b.as<Pair>(), nvb, it, maxit, st));
-                b.iter_base = 0;
+                b.iter_base = b.iter_now = 0;
             }
             b.outer++;
         }
@@ -1754,7 +1786,9 @@ struct BatchSolver {
         }
         CKH(hipMemcpyAsync(runs.p, h_runs, (size_t)np * sizeof(BatchRun), hipMemcpyHostToDevice, st));
         for (StepSet &K : set) {
-            auto in_set = [&](int j) { return pb[j]->phase == kPhaseRun && pb[j]->f32 == K.f32; };
+            auto in_set = [&](int j) {
+                return pb[j]->phase == kPhaseRun && !pb[j]->resident && pb[j]->f32 == K.f32;
+            };
             int na = 0;
             for (int j = 0; j < np; j++)
                 if (in_set(j))
@@ -1831,6 +1865,162 @@ struct BatchSolver {
         return EXCMG_OK;
     }
 
+    // One resident launch: the running systems with the most work ahead of them that fit
+    // together, each on the smallest share of the CUs that holds it; what is left of the 256
+    // goes to those with the slowest iterations.  (Small shares: a system on twice the CUs is
+    // less than twice as fast, so they finish more systems per second, and the large ones are
+    // the last to be alone.)  A launch ends when one of its runs has stopped, but not before
+    // kBatchWindow, so that stops and restarts come together, nor, with `others` waiting for
+    // steps, after kBatchTurn.
+    static constexpr double kBatchWindow = 500.0, kBatchTurn = 4000.0;   // us
+    int launch_resident(bool others) {
+        res.now.clear();
+        if (res.off) return EXCMG_OK;
+        struct Pick { int j, share; double ahead; };
+        std::vector<Pick> all;
+        for (int j = 0; j < (int)pb.size(); j++) {
+            BProb &b = *pb[j];
+            if (b.phase != kPhaseRun || !b.resident) continue;
+            double ahead = 0.0;      // iterations grow as N, their work as N^3
+            for (int l = b.level; l < b.nl; l++) ahead += std::pow((double)b.lv[l].N, 4.0);
+            const auto &P = res.of(b.lv[b.level].n, !b.f32);
+            int k = 0;
+            while (P.share[k].blocks == 0) k++;
+            all.push_back({j, k, ahead});
+        }
+        if (all.empty()) return EXCMG_OK;
+        std::sort(all.begin(), all.end(), [](const Pick &a, const Pick &b) {
+            return a.ahead != b.ahead ? a.ahead > b.ahead : a.j < b.j;
+        });
+        auto plan = [&](const Pick &p) -> const ResidentPlan & {
+            const BProb &b = *pb[p.j];
+            return res.of(b.lv[b.level].n, !b.f32).share[p.share];
+        };
+        std::vector<Pick> run;
+        int left = batch_share(kBatchShares - 1);
+        for (const Pick &p : all)
+            if (plan(p).blocks <= left) {
+                run.push_back(p);
+                left -= plan(p).blocks;
+            }
+        for (;;) {
+            Pick *slow = nullptr, next{};
+            for (Pick &p : run) {
+                Pick q = p;
+                while (++q.share < kBatchShares)
+                    if (plan(q).us < plan(p).us) break;
+                if (q.share == kBatchShares || plan(q).blocks - plan(p).blocks > left) continue;
+                if (!slow || plan(p).us > plan(*slow).us) {
+                    slow = &p;
+                    next = q;
+                }
+            }
+            if (!slow) break;
+            left -= plan(next).blocks - plan(*slow).blocks;
+            *slow = next;
+        }
+        size_t cell_bytes = 0, lds = 0;
+        unsigned steps = 0;
+        for (const Pick &p : run) {
+            cell_bytes += plan(p).exchange;
+            lds = std::max(lds, plan(p).lds);
+            const BProb &b = *pb[p.j];
+            steps = std::max(steps, (unsigned)std::max(0, maxit - b.iter_now) + 2);
+        }
+        const size_t slot_bytes = 6 * 256 * 16, np = pb.size();
+        const bool wrap = res.epoch + steps < res.epoch;
+        if (wrap || res.cells.bytes < cell_bytes || !res.h_table) {
+            if (!res.h_table)
+                CKH(hipHostMalloc((void **)&res.h_table, np * sizeof(ResidentBatchRun), hipHostMallocDefault));
+            if (res.cells.ensure(cell_bytes) != EXCMG_OK || res.slots.ensure(np * slot_bytes) != EXCMG_OK ||
+                res.flags.ensure((np + 1) * sizeof(unsigned)) != EXCMG_OK ||
+                res.table.ensure(np * sizeof(ResidentBatchRun)) != EXCMG_OK) {
+                g_err[0] = 0;      // (no room: the steps need none)
+                return resident_stop();
+            }
+            CKH(hipMemsetAsync(res.slots.p, 0, res.slots.bytes, st));
+            CKH(hipMemsetAsync(res.flags.p, 0, res.flags.bytes, st));
+            res.epoch = 0;
+        }
+        int blocks = 0;
+        size_t cell0 = 0;
+        for (size_t k = 0; k < run.size(); k++) {
+            BProb &b = *pb[run[k].j];
+            Level &Lv = b.lv[b.level];
+            const ResidentPlan &P = plan(run[k]);
+            ResidentBatchRun &E = res.h_table[k];
+            E = ResidentBatchRun{};
+            E.first = blocks;
+            E.blocks = P.blocks;
+            E.threads = P.threads;
+            E.kind = batch_kind(!b.f32, P.C, P.rs);
+            ResidentRun<double> &R = E.run;
+            R.n = Lv.n;
+            R.nbx = P.nbx;
+            R.nby = P.nby;
+            R.bx = P.bx;
+            R.by = P.by;
+            R.bz = P.bz;
+            R.sgn = Lv.g1.sgn;
+            R.r = b.r.as<double>();
+            R.rs = b.rs.as<double>();
+            for (int q = 0; q < 2; q++) {
+                R.p[q] = b.p[q].as<double>();
+                R.ps[q] = b.ps[q].as<double>();
+            }
+            R.x = R.x_work = Lv.x.as<double>();
+            R.state = S(run[k].j);
+            R.cells = (char *)res.cells.p + cell0;
+            R.slots = (char *)res.slots.p + k * slot_bytes;
+            R.epoch = res.epoch;
+            R.min_steps = (unsigned)std::max(1.0, kBatchWindow / P.us);
+            R.max_steps = others ? (unsigned)std::max(1.0, kBatchTurn / P.us) : ~0u;
+            R.stop = res.flags.as<unsigned>();
+            R.halt = res.flags.as<unsigned>() + 1 + k;
+            blocks += P.blocks;
+            cell0 += P.exchange;
+            res.now.push_back(run[k].j);
+        }
+        CKH(hipMemcpyAsync(res.table.p, res.h_table, run.size() * sizeof(ResidentBatchRun),
+                           hipMemcpyHostToDevice, st));
+        if (resident_batch(res.table.as<ResidentBatchRun>(), (int)run.size(), blocks, lds, st) != hipSuccess) {
+            (void)hipGetLastError();
+            return resident_stop();
+        }
+        return EXCMG_OK;
+    }
+
+    // From here on the steps take every system.
+    int resident_stop() {
+        res.off = true;
+        res.now.clear();
+        for (BProb *b : pb) b->resident = false;
+        return EXCMG_OK;
+    }
+
+    // After a resident launch, with the states read.  A run whose wait ran out left its
+    // vectors partly written: its level goes on from the residual of the iterate it has.
+    int resident_done() {
+        bool late = false;
+        unsigned used = 0;
+        for (int j : res.now) {
+            BProb &b = *pb[j];
+            if (h_states[j].err) {
+                late = true;
+                b.phase = kPhaseCheck;
+                b.prev = INFINITY;
+                h_states[j].err = 0;
+                h_states[j].status = kBreakdown;
+                CKH(hipMemcpyAsync(S(j), &h_states[j], sizeof(BicgState), hipMemcpyHostToDevice, st));
+            } else {
+                used = std::max(used, (unsigned)(h_states[j].iter - b.iter_now));
+                b.iter_now = h_states[j].iter;
+            }
+        }
+        res.epoch += used + 2;
+        return late ? resident_stop() : EXCMG_OK;
+    }
+
     int run() {
         const int np = (int)pb.size();
         for (int j = 0; j < np; j++) CKR(start(j));
@@ -1853,14 +2043,30 @@ struct BatchSolver {
             bool running = false;
             for (int j = 0; j < np; j++) running |= (pb[j]->phase == kPhaseRun);
             if (!running) break;
+            // systems that fit on the chip run resident, the others by steps
+            for (int j = 0; j < np; j++) {
+                BProb &b = *pb[j];
+                if (b.phase != kPhaseRun) continue;
+                b.resident = !persistent && !res.off &&
+                             res.of(b.lv[b.level].n, !b.f32).share[kBatchShares - 1].blocks > 0;
+            }
             CKR(build_items());
-            // advance every running system until one of them stops
+            // advance the running systems until one of them stops
             for (;;) {
-                CKR(launch_steps());
+                const bool steps = set[0].ni > 0 || set[1].ni > 0;
+                const bool was_off = res.off;
+                if (steps) CKR(launch_steps());
+                CKR(launch_resident(steps));
                 CKH(hipMemcpyAsync(h_states, states.p, (size_t)np * sizeof(BicgState),
                                    hipMemcpyDeviceToHost, st));
+                int err[2] = {0, 0};
+                for (int k = 0; steps && k < 2; k++)
+                    CKH(hipMemcpyAsync(&err[k], (char *)set[k].ctl.p + offsetof(BatchCtl, error),
+                                       sizeof(int), hipMemcpyDeviceToHost, st));
                 CKH(hipStreamSynchronize(st));
-                bool changed = false;
+                if (err[0] || err[1]) return fail(EXCMG_EHIP, "batched step: a bounded wait expired");
+                CKR(resident_done());
+                bool changed = res.off != was_off;
                 for (int j = 0; j < np; j++) {
                     BProb &b = *pb[j];
                     if (b.phase != kPhaseRun || h_states[j].status == kRunning) continue;
@@ -1870,12 +2076,6 @@ struct BatchSolver {
                     b.phase = kPhaseCheck;
                     if (h_states[j].status == kBreakdown) b.broke = 1;
                 }
-                int err[2] = {0, 0};
-                for (int k = 0; k < 2; k++)
-                    CKH(hipMemcpyAsync(&err[k], (char *)set[k].ctl.p + offsetof(BatchCtl, error),
-                                       sizeof(int), hipMemcpyDeviceToHost, st));
-                CKH(hipStreamSynchronize(st));
-                if (err[0] || err[1]) return fail(EXCMG_EHIP, "batched step: a bounded wait expired");
                 if (changed) break;
             }
         }

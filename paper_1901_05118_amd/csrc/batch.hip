@@ -1,6 +1,7 @@
-// Batched Bi-CG: every running system of a batch (systems of different grid sizes and boundary
-// kinds, each with its own scalars) advances by one iteration of Algorithm 2 per step, in one
-// of two forms:
+// Batched Bi-CG by steps: every running system of a batch that does not fit on the chip (those
+// that do run in shared resident launches, see resident.hip; systems of different grid sizes
+// and boundary kinds, each with its own scalars) advances by one iteration of Algorithm 2 per
+// step, in one of two forms:
 //  * phase kernels (default): sweep A over the tiles of all systems, alpha per system, sweep B
 //    over the chunks of all systems, beta per system -- four grid-stride launches with no
 //    communication between workgroups inside a launch, captured G steps at a time in a
@@ -8,7 +9,8 @@
 //  * one persistent launch per step (below).  Inside a launch the workgroups hand results to
 //    each other, which on MI355X needs an agent-scope release/acquire per work item (an L2
 //    write-back and invalidate on each XCD); measured, this costs more than the three kernel
-//    boundaries it removes, so it is the second choice.
+//    boundaries it removes, so it is the second choice (asked for by the caller, it takes every
+//    system).
 //
 // Persistent form.  Work queue.  A launch processes a list of items claimed in order through one atomic
 // counter: first every sweep-A item (one z-marched stencil tile of one system: direction

@@ -221,12 +221,13 @@ struct ResidentPlan {
     int rs = 0;                    // row stride of the LDS box
     int threads = 0, blocks = 0;
     size_t lds = 0, exchange = 0;  // bytes of LDS; of exchanged cells
+    double us = 0.0;               // modelled time of an iteration
 };
 template <typename T>
 struct ResidentRun {
     int n, nbx, nby, bx, by, bz;
     double sgn;                    // fictitious-point sign (Geom::sgn)
-    const T *r, *rs;               // residuals at the start (or at a resumption)
+    T *r, *rs;                     // residuals at the start (or at a resumption)
     T *p[2], *ps[2];               // directions: read at a resumption, written at the end
     const double *x;               // iterate at the start
     double *x_work;                // iterate of the run (the caller's is left alone)
@@ -236,10 +237,28 @@ struct ResidentRun {
     void *cells;                   // exchanged cells (ResidentPlan::exchange bytes)
     void *slots;                   // exchanged partials: 6 planes of 16 bytes per workgroup (256)
     unsigned epoch;                // the run's exchanges are numbered from epoch + 1
+    // a run of a batch (r and r* are also written when it is halted; x_work may be x)
+    unsigned min_steps, max_steps; // iterations before it may be, and is, halted
+    unsigned *stop;                // the launch's: epoch + 1 once a run has stopped
+    unsigned *halt;                // this run's: the exchange after which it is halted
 };
 bool resident_plan(int n, int dim, bool fp64, ResidentPlan &plan);
 template <typename T>
 hipError_t resident_run(const ResidentPlan &plan, const ResidentRun<T> &run, hipStream_t st);
+
+// Several 3D runs in one cooperative launch, each on its share of the workgroups.
+constexpr int kBatchShares = 6;
+constexpr int batch_share(int k) { return 8 << k; }       // 8 .. 256 workgroups
+// the cheapest partition within each share (blocks == 0: none)
+void resident_batch_plans(int n, bool fp64, ResidentPlan (&plans)[kBatchShares]);
+constexpr int batch_kind(bool fp64, int C, int rs) { return (C * 64 + rs) * 2 + (fp64 ? 1 : 0); }
+struct ResidentBatchRun {
+    ResidentRun<double> run;       // (FP32 runs: the vectors are float)
+    int first, blocks, threads;    // workgroups first .. first + blocks - 1
+    int kind;                      // batch_kind of its partition
+};
+hipError_t resident_batch(const ResidentBatchRun *runs, int count, int blocks, size_t lds,
+                          hipStream_t st);
 
 // ---------------------------------------------------------------- level kernels
 

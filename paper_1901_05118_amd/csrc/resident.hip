@@ -304,8 +304,7 @@ __device__ __forceinline__ bool halo_cell(int h, int bx, int by, int bz, int &x,
     return false;
 }
 
-// One run.  C: consecutive z-cells per thread; NH: halo cells per thread; MT: the largest
-// workgroup (threads); MULTI: more than one brick.
+// A run of its own.  MT: the largest workgroup (threads).
 template <int DIM, typename T, int C, int RS, int NH, int MT, bool MULTI>
 __global__ void __launch_bounds__(MT) k_resident(ResidentRun<T> a) {
     extern __shared__ char lds_raw[];
@@ -313,408 +312,9 @@ __global__ void __launch_bounds__(MT) k_resident(ResidentRun<T> a) {
     __shared__ Pair all_a[4], all_b[8];
     __shared__ int bad;
     T *M = (T *)lds_raw;
-    int tid = threadIdx.x;
-    const int nt = blockDim.x, nw = nt >> 6;
-    const int W = MULTI ? gridDim.x : 1, blk = MULTI ? blockIdx.x : 0;
-    const int n = a.n, bx = a.bx, by = a.by, bz = a.bz;
-    const int x0 = (blk % a.nbx) * bx, y0 = ((blk / a.nbx) % a.nby) * by,
-              z0 = (blk / (a.nbx * a.nby)) * bz;
-    const int groups = (bz + C - 1) / C;
-    constexpr int BX = RS;
-    constexpr int HY = DIM == 3 ? 2 : 0;       // halo rows in y
-    const int ny = DIM == 3 ? n : 1;
-    const int PS = DIM == 3 ? BX * (by + 4) : BX, LE = PS * (groups * C + 4);
-    BicgState *S = a.state;
-    int status = S->status, iter = S->iter;
-    if (status != kRunning) return;            // uniform
-
-    // the box of the marched array; one more element takes what has no place in it
-    for (int e = tid; e <= LE; e += nt) M[e] = (T)0;
-    if (tid == 0) bad = 0;
-    if (tid < 4) all_a[tid] = all_b[2 * tid] = all_b[2 * tid + 1] = Pair{0.0, 0.0};
-
-    // this thread's column of C cells (those from `cells` on are none)
-    const int lx = tid % bx, ly = (tid / bx) % by, lg = tid / (bx * by);
-    const int gx = x0 + lx, gy = y0 + ly, gz = z0 + lg * C;
-    int cells = (lg < groups && gx < n && gy < ny) ? max(0, min(C, min(n, z0 + bz) - gz)) : 0;
-    int ob = ((min(lg, groups - 1) * C + 2) * (by + 2 * HY) + ly + HY) * BX + lx + 2;
-    int gi = cells > 0 ? (gz * ny + gy) * n + gx : 0;
-    const int gplane = cells > 0 ? ny * n : 0;
-    // fictitious points that mirror this column
-    const int ghx = cells == 0 ? 0 : gx == 0 ? -2 : (gx == n - 1 ? 2 : 0);
-    const int ghy = cells == 0 || DIM == 2 ? 0 : gy == 0 ? -2 * BX : (gy == n - 1 ? 2 * BX : 0);
-    const int ghz0 = cells > 0 && gz == 0, ghz1 = cells > 0 && gz + cells == n;
-    // Mailboxes: the halo cells of a brick, in the order of halo_cell, in one piece of memory.
-    // This thread reads cells tid, tid + nt, ... of its own box, and sends the same cells of
-    // its neighbours' boxes, as far as this brick owns them (bricks but the last of an axis
-    // are whole, so cell h of a neighbour's box is owned by the brick on the other side).
-    const int hn = DIM == 3 ? 4 * (bx * by + bx * bz + by * bz + bx + by + bz) : 4 * (bx + bz + 1);
-    const __amdgpu_buffer_rsrc_t xc = exchange_rsrc(a.cells, 2u * sizeof(T) * (unsigned)(W * hn)),
-                                 xs = exchange_rsrc(a.slots, 6 * kSlotPlane);
-    const int own = bx * by * groups * C;     // staged r and r* of the brick: R, R + own
-    T *R = M + LE + 1;
-    const int os = cells > 0 ? (lg * C * by + ly) * bx + lx : 0, oplane = bx * by;
-    int hplace[MULTI ? NH : 1];               // place in LDS (LE: none) | staged source << 16
-    unsigned hdest[MULTI ? NH : 1];           // cell of a neighbour's box (kNoCell: none)
-    T hr[MULTI ? NH : 1], hs[MULTI ? NH : 1], hv[MULTI ? NH : 1];  // r, r*, the direction not in LDS
-    if (MULTI) {
-#pragma nounroll
-        for (int q = 0; q < NH; q++) {
-            // (a scratch-free loop: every trip decodes slot q and keeps it by selects)
-            int x, y, z, place = LE;
-            unsigned dest = kNoCell;
-            const int h = tid + q * nt;
-            if (halo_cell<DIM>(h, bx, by, bz, x, y, z)) {
-                const int X = x0 + x, Y = y0 + y, Z = z0 + z;
-                if (X >= 0 && X < n && Y >= 0 && Y < ny && Z >= 0 && Z < n)
-                    place = ((z + 2) * (by + 2 * HY) + y + HY) * BX + x + 2;
-                // the brick that has cell h of its box here, and the cell's place in this one
-                const int dx = x < 0 ? 1 : (x >= bx ? -1 : 0), dy = y < 0 ? 1 : (y >= by ? -1 : 0),
-                          dz = z < 0 ? 1 : (z >= bz ? -1 : 0);
-                const int X0 = x0 + dx * bx, Y0 = y0 + dy * by, Z0 = z0 + dz * bz;
-                const int sx = x + dx * bx, sy = y + dy * by, sz = z + dz * bz;
-                if (X0 >= 0 && X0 < n && Y0 >= 0 && Y0 < ny && Z0 >= 0 && Z0 < n && x0 + sx < n &&
-                    y0 + sy < ny && z0 + sz < n) {
-                    dest = (unsigned)((blk + dx + a.nbx * (dy + a.nby * dz)) * hn + h);
-                    place |= ((sz * by + sy) * bx + sx) << 16;
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < NH; u++) {
-                hplace[u] = u == q ? place : (q == 0 ? LE : hplace[u]);
-                hdest[u] = u == q ? dest : (q == 0 ? kNoCell : hdest[u]);
-            }
-        }
-    }
-    auto hoff = [&](int q) { return hplace[q] & 0xffff; };
-
-    // own values into LDS, and into the fictitious points that mirror them
-    const bool edge = ghx || ghy || ghz0 || ghz1;
-    auto place = [&](const T (&v)[C]) {
-#pragma unroll
-        for (int c = 0; c < C; c++) M[c < cells ? ob + c * PS : LE] = v[c];
-        if (edge) {
-            const bool neg = a.sgn < 0;
-#pragma unroll
-            for (int c = 0; c < C; c++) {
-                if (c < cells) {
-                    T *P = M + ob + c * PS;
-                    const T g = neg ? -v[c] : v[c];
-                    if (ghx) P[ghx] = g;
-                    if (ghy) P[ghy] = g;
-                    if (c == 0 && ghz0) P[-2 * PS] = g;
-                    if (c == cells - 1 && ghz1) P[2 * PS] = g;
-                }
-            }
-        }
-    };
-
-    // ---- start or resume: scalars, then r, r*, p, p* of the brick and its halo
-    const int maxit = S->maxit;
-    const double thr = S->thr;
-    double rho = S->rho, rr = S->rr, beta = 0.0, alpha = S->alpha, sigma = S->sigma;
-    double rho_old = rho;
-    const bool first = (iter == 0);
-    __syncthreads();
-    if (!first) {
-        // rho of the replaced residual and the checks of the loop (see link_step)
-        rho_old = S->rho_slot[(iter & 1) ^ 1];
-        Pair v[2];
-        merge_fixed<2>(a.part, a.part_count, v, red);
-        rho = pair_value(v[0]);
-        rr = pair_value(v[1]);
-        if (rr <= thr) status = kConverged;
-        else if (iter >= maxit) status = kNoConv;
-        else if (rho == 0.0 || !isfinite(rho)) status = kBreakdown;
-        beta = rho / rho_old;
-    }
-
-    // In the first iteration of a run p = r and p* = r*: the old directions are zeros and
-    // beta is 0.
-    T r[C], s[C], o[C];      // r, r*, and p while LDS holds p* (p* while it holds p)
-    double xv[C];            // the iterate
-    {
-        const T *p = a.p[iter & 1], *ps = a.ps[iter & 1];
-#pragma unroll
-        for (int c = 0; c < C; c++) {
-            r[c] = s[c] = o[c] = (T)0;
-            xv[c] = 0.0;
-            if (c < cells) {
-                const unsigned i = gi + c * gplane;
-                r[c] = a.r[i];
-                s[c] = a.rs[i];
-                xv[c] = a.x[i];
-                if (!first) {
-                    o[c] = p[i];
-                    M[ob + c * PS] = ps[i];
-                }
-            }
-        }
-        if (MULTI) {
-#pragma unroll
-            for (int q = 0; q < NH; q++) {
-                hr[q] = hs[q] = hv[q] = (T)0;
-                int x, y, z;
-                if (hoff(q) != LE && halo_cell<DIM>(tid + q * nt, bx, by, bz, x, y, z)) {
-                    const unsigned i = (unsigned)(((z0 + z) * ny + y0 + y) * n + x0 + x);
-                    hr[q] = a.r[i];
-                    hs[q] = a.rs[i];
-                    if (!first) {
-                        hv[q] = p[i];
-                        M[hoff(q)] = ps[i];
-                    }
-                }
-            }
-        }
-    }
-    unsigned ep = a.epoch;
-    // Phases of an iteration are kept apart in the registers: addresses and FP64 forms of FP32
-    // values that one phase derives are not carried into the next.
-    auto keep = [&]() {
-        asm volatile("" : "+v"(ob), "+v"(cells));
-        if constexpr (sizeof(T) == 4) {
-#pragma unroll
-            for (int c = 0; c < C; c++) asm volatile("" : "+v"(r[c]), "+v"(s[c]), "+v"(o[c]));
-        }
-        if (MULTI) {
-#pragma unroll
-            for (int q = 0; q < NH; q++) asm volatile("" : "+v"(hplace[q]), "+v"(hdest[q]));
-        }
-    };
-
-    auto stencil = [&](auto emit) {
-        const T *B = M + (ob - 2 * PS - HY * RS - 2);
-        if constexpr (DIM == 3) column_outputs<C, RS, T>(B, PS, emit);
-        else column_outputs_2d<C, T>(B, PS, emit);
-    };
-
-    while (status == kRunning) {
-        ep++;
-        asm volatile("" : "+v"(tid));
-        const int lane = tid & 63, wave = tid >> 6;
-        keep();
-        // ---- directions: p into LDS, p* into o and hv
-        T ho[MULTI ? NH : 1];
-        {
-            T pn[C], so[C];
-#pragma unroll
-            for (int c = 0; c < C; c++) so[c] = M[ob + c * PS];
-            if (MULTI) {
-#pragma unroll
-                for (int q = 0; q < NH; q++) ho[q] = M[hoff(q)];
-            }
-#pragma unroll
-            for (int c = 0; c < C; c++) {
-                pn[c] = (T)((double)r[c] + beta * (double)o[c]);
-                o[c] = (T)((double)s[c] + beta * (c < cells ? (double)so[c] : 0.0));
-            }
-            place(pn);
-        }
-        if (MULTI) {
-#pragma unroll
-            for (int q = 0; q < NH; q++)
-                M[hoff(q)] = (T)((double)hr[q] + beta * (double)hv[q]);
-#pragma unroll
-            for (int q = 0; q < NH; q++) hv[q] = (T)((double)hs[q] + beta * (double)ho[q]);
-        }
-        __syncthreads();
-        keep();
-
-        // ---- q = A p, sigma = p*.q
-        T qv[C], qs[C];
-        Pair sg[1] = {{0.0, 0.0}};
-        stencil([&](int c, double y) {
-            qv[c] = c < cells ? (T)y : (T)0;
-            dot2_acc(sg[0], (double)o[c], (double)qv[c]);
-            // (one output after the other)
-            if (C >= 8) asm volatile("" : "+v"(sg[0].s), "+v"(sg[0].c), "+v"(qv[c]));
-        });
-        wave_merge_n<1>(sg);
-        if (lane == 0) red[wave] = sg[0];
-        __syncthreads();     // also: every thread has read p
-        if (wave == 0) {
-            Pair v[1] = {lane < nw ? red[lane] : Pair{0.0, 0.0}};
-            row_merge_n<1>(v);
-            if (MULTI) {
-                if (lane < 2) {
-                    const double b = lane == 0 ? v[0].s : v[0].c;
-                    put(xs, 16u * (unsigned)blk + lane * kSlotPlane, 0, low(b), high(b), ep);
-                }
-            } else if (lane == 0) {
-                all_a[0] = v[0];
-            }
-        }
-        // ---- p* into LDS, p into o and hv; q* = A^T p*
-        keep();
-        {
-            T pv[C];
-#pragma unroll
-            for (int c = 0; c < C; c++) pv[c] = M[ob + c * PS];
-            if (MULTI) {
-#pragma unroll
-                for (int q = 0; q < NH; q++) ho[q] = M[hoff(q)];
-            }
-            place(o);
-#pragma unroll
-            for (int c = 0; c < C; c++) o[c] = c < cells ? pv[c] : (T)0;
-        }
-        if (MULTI) {
-#pragma unroll
-            for (int q = 0; q < NH; q++) {
-                M[hoff(q)] = hv[q];
-                hv[q] = ho[q];
-            }
-        }
-        __syncthreads();
-        keep();
-        stencil([&](int c, double y) {
-            qs[c] = c < cells ? (T)y : (T)0;
-            if (C >= 8) asm volatile("" : "+v"(qs[c]));
-        });
-        // (q* is formed here, before the wait, not carried over it as its 21 C terms)
-#pragma unroll
-        for (int c = 0; c < C; c++) asm volatile("" : "+v"(qs[c]));
-
-        // ---- sigma and alpha
-        if (MULTI) {
-            if (64 * wave < W) {
-                const Pair v = gather_pairs(xs, tid < W ? 16u * (unsigned)tid : kNoPlace, 0, ep, &bad);
-                if (lane == 0) all_a[wave] = v;
-            }
-            __syncthreads();
-            if (bad) break;
-        }
-        {
-            Pair v = all_a[0];
-            if (W > 64) v = pair_merge(pair_merge(v, all_a[1]), pair_merge(all_a[2], all_a[3]));
-            sigma = wave_uniform(pair_value(v));
-        }
-        if (sigma == 0.0 || !isfinite(sigma)) {
-            status = kBreakdown;
-            break;
-        }
-        alpha = wave_uniform(rho / sigma);
-        iter++;
-
-        keep();
-        // ---- r -= alpha q, r* -= alpha q*; rho' = r*.r and r.r; x += alpha p
-        Pair dt[2] = {{0.0, 0.0}, {0.0, 0.0}};
-#pragma unroll
-        for (int c = 0; c < C; c++) {
-            r[c] = (T)((double)r[c] - alpha * (double)qv[c]);
-            s[c] = (T)((double)s[c] - alpha * (double)qs[c]);
-            if (MULTI && c < cells) {
-                R[os + c * oplane] = r[c];
-                R[own + os + c * oplane] = s[c];
-            }
-        }
-        if (MULTI) {
-            __syncthreads();
-#pragma unroll
-            for (int q = 0; q < NH; q++) {
-                const int src = (unsigned)hplace[q] >> 16;
-                put_cell(xc, hdest[q], R[src], R[own + src]);
-            }
-        }
-        keep();
-#pragma unroll
-        for (int c = 0; c < C; c++) {
-            dot2_acc(dt[0], (double)s[c], (double)r[c]);
-            dot2_acc(dt[1], (double)r[c], (double)r[c]);
-            xv[c] = xv[c] + alpha * (double)o[c];
-        }
-        wave_merge_n<2>(dt);
-        if (lane == 0) {
-            red[2 * wave] = dt[0];
-            red[2 * wave + 1] = dt[1];
-        }
-        // the sent cells have arrived (stores past the L2) before the partials announce them
-        if (MULTI) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-        if (wave == 0) {
-            Pair v[2] = {{0.0, 0.0}, {0.0, 0.0}};
-            if (lane < nw) {
-                v[0] = red[2 * lane];
-                v[1] = red[2 * lane + 1];
-            }
-            row_merge_n<2>(v);
-            if (MULTI) {
-                if (lane < 4) {
-                    const Pair pv = lane < 2 ? v[0] : v[1];
-                    const double b = (lane & 1) ? pv.c : pv.s;
-                    put(xs, 16u * (unsigned)blk + (2 + lane) * kSlotPlane, 0, low(b), high(b), ep);
-                }
-            } else if (lane == 0) {
-                all_b[0] = v[0];
-                all_b[1] = v[1];
-            }
-        }
-        if (MULTI) {
-            // A load takes about 1800 cycles (past the L2); asked too early it is asked twice.
-            __builtin_amdgcn_s_sleep(kFirstLook);
-            if (64 * (wave >> 1) < W) {     // even waves: rho', odd waves: r.r
-                const int w = (wave >> 1) * 64 + lane;
-                const Pair v = gather_pairs(xs, w < W ? 16u * (unsigned)w : kNoPlace,
-                                            (2 + 2 * (wave & 1)) * kSlotPlane, ep, &bad);
-                if (lane == 0) all_b[wave] = v;
-            }
-            __syncthreads();
-            // all partials are here, so all cells are: r and r* of the halo (a cell of the box
-            // that the grid does not have reads as anything and goes nowhere)
-            unsigned cell = (unsigned)(blk * hn + tid);
-#pragma unroll
-            for (int q = 0; q < NH; q++, cell += nt) get_cell(xc, cell, hr[q], hs[q]);
-        } else {
-            __syncthreads();
-        }
-        if (MULTI && bad) break;
-        // ---- end of the iteration: the stopping checks in the order of the loop, then beta
-        rho_old = rho;
-        {
-            Pair v[2] = {all_b[0], all_b[1]};
-            if (W > 64) {
-#pragma unroll
-                for (int q = 0; q < 2; q++)
-                    v[q] = pair_merge(pair_merge(v[q], all_b[2 + q]),
-                                      pair_merge(all_b[4 + q], all_b[6 + q]));
-            }
-            rho = wave_uniform(pair_value(v[0]));
-            rr = wave_uniform(pair_value(v[1]));
-        }
-        if (rr <= thr) status = kConverged;
-        else if (iter >= maxit) status = kNoConv;
-        else if (rho == 0.0 || !isfinite(rho)) status = kBreakdown;
-        beta = wave_uniform(rho / rho_old);
-    }
-    if (MULTI && bad) {
-        if (tid == 0) atomicExch(&S->err, 1);
-        return;
-    }
-    // the iterate, and the directions for a run that goes on after its residuals are replaced
-    {
-        T *p = a.p[iter & 1], *ps = a.ps[iter & 1];
-#pragma unroll
-        for (int c = 0; c < C; c++) {
-            if (c < cells) {
-                const unsigned i = gi + c * gplane;
-                a.x_work[i] = xv[c];
-                p[i] = o[c];
-                ps[i] = M[ob + c * PS];
-            }
-        }
-    }
-    if (blk == 0 && tid == 0) {
-        S->rr = rr;
-        S->rho = rho;
-        S->rho_slot[iter & 1] = rho;
-        S->rho_slot[(iter & 1) ^ 1] = rho_old;
-        S->alpha = alpha;
-        S->beta = beta;
-        S->sigma = sigma;
-        S->iter = iter;
-        S->status = status;
-        S->poll_status = status;
-    }
+    constexpr bool BATCH = false;
+    const int blk = MULTI ? blockIdx.x : 0, W = MULTI ? gridDim.x : 1, nt = blockDim.x;
+#include "resident_body.hpp"
 }
 
 template <int DIM, typename T, int C, int RS, int NH, int MT>
@@ -734,11 +334,16 @@ constexpr int halo_slots(int C, int dim) { return dim == 2 ? 2 : C <= 2 ? 4 : C 
 constexpr int max_threads(int C, bool fp64, int dim) {
     return C == 16 && (fp64 || dim == 2) ? 0 : C <= 2 && !fp64 ? 1024 : 512;
 }
+// (a run of a batch: FP32 with at least 4 cells per thread)
+constexpr int max_batch_threads(int C, bool fp64) {
+    return C == 16 && fp64 ? 0 : C <= 2 && !fp64 ? 0 : 512;
+}
 constexpr size_t kMaxLds = 158 * 1024;     // of 160 KB per workgroup; the rest is static
 
 // Partition of the grid into nbx x nby x nbz bricks (2D: rows are z, nby = 1) with C cells
 // per thread; false if the kernels cannot take it.
-bool try_plan(int n, int dim, bool fp64, int nbx, int nby, int nbz, int C, ResidentPlan &p) {
+bool try_plan(int n, int dim, bool fp64, bool batch, int nbx, int nby, int nbz, int C,
+              ResidentPlan &p) {
     const int ny = dim == 2 ? 1 : n;
     p.bx = (n + nbx - 1) / nbx;
     p.by = (ny + nby - 1) / nby;
@@ -758,7 +363,8 @@ bool try_plan(int n, int dim, bool fp64, int nbx, int nby, int nbz, int C, Resid
     // at least the four waves of merge_fixed, and two waves per 64 workgroups to gather the
     // partials of rho' and r.r
     const long long waves = std::max({4LL, (columns + 63) / 64, (p.blocks + 63) / 64 * 2LL});
-    if (64 * waves > max_threads(C, fp64, dim)) return false;
+    if (64 * waves > (batch ? max_batch_threads(C, fp64) : max_threads(C, fp64, dim))) return false;
+    if (batch && one) return false;
     p.threads = (int)(64 * waves);
     const long long halo = dim == 2 ? 4LL * (p.bx + p.bz + 1)
                                     : 4LL * (p.bx * p.by + p.bx * p.bz + p.by * p.bz + p.bx + p.by + p.bz);
@@ -769,6 +375,30 @@ bool try_plan(int n, int dim, bool fp64, int nbx, int nby, int nbz, int C, Resid
     if (!one) p.lds += 2 * (size_t)columns * C * es;
     p.exchange = one ? 0 : (size_t)p.blocks * halo * 2 * es;
     return p.lds <= kMaxLds;
+}
+
+// Every partition that the kernels can take, with its modelled time of an iteration.
+template <class Use>
+void for_plans(int n, int dim, bool fp64, bool batch, Use use) {
+    if (n < 7 || n > (dim == 2 ? 1024 : 128)) return;
+    const int most = dim == 2 ? kMaxGroups : 16;
+    auto whole = [&](int k) { return (n + (n + k - 1) / k - 1) / ((n + k - 1) / k) == k; };
+    for (int C : {1, 2, 4, 8, 16})
+        for (int bz = 1; bz <= most; bz++)
+            for (int by = 1; by <= (dim == 2 ? 1 : most); by++)
+                for (int bx = 1; bx <= (dim == 2 ? 32 : 8) && bx * by * bz <= kMaxGroups; bx++) {
+                    ResidentPlan p;
+                    // (a number of bricks per axis that rounds to a smaller one comes up there)
+                    if (!whole(bz) || !whole(bx) || (dim == 3 && !whole(by))) continue;
+                    if (!try_plan(n, dim, fp64, batch, bx, by, bz, C, p)) continue;
+                    const double waves = p.threads / 64, W = p.blocks;
+                    p.us = 0.056 * waves * C + 0.086 * waves + 0.36 * C;
+                    if (p.blocks > 1)
+                        p.us += 0.83 + 0.094 * W / 64 + 0.32 * ((p.blocks + 63) / 64) +
+                                0.048 * waves * halo_slots(C, dim) +
+                                2.1e-7 * (double)p.exchange * (fp64 ? 1 : 2);
+                    use(p);
+                }
 }
 
 }  // namespace
@@ -785,27 +415,19 @@ bool try_plan(int n, int dim, bool fp64, int nbx, int nby, int nbz, int C, Resid
 // than the 256 registers of 512 threads), nor do planes above about 1000^2; smaller grids are
 // levels solved directly.
 bool resident_plan(int n, int dim, bool fp64, ResidentPlan &plan) {
-    if (n < 7 || n > (dim == 2 ? 1024 : 128)) return false;
-    double best = 1e30;
-    const int most = dim == 2 ? kMaxGroups : 16;
-    for (int C : {1, 2, 4, 8, 16})
-        for (int bz = 1; bz <= most; bz++)
-            for (int by = 1; by <= (dim == 2 ? 1 : most); by++)
-                for (int bx = 1; bx <= (dim == 2 ? 32 : 8) && bx * by * bz <= kMaxGroups; bx++) {
-                    ResidentPlan p;
-                    if (!try_plan(n, dim, fp64, bx, by, bz, C, p)) continue;
-                    const double waves = p.threads / 64, W = p.blocks;
-                    double t = 0.056 * waves * C + 0.086 * waves + 0.36 * C;
-                    if (p.blocks > 1)
-                        t += 0.83 + 0.094 * W / 64 + 0.32 * ((p.blocks + 63) / 64) +
-                             0.048 * waves * halo_slots(C, dim) +
-                             2.1e-7 * (double)p.exchange * (fp64 ? 1 : 2);
-                    if (t < best) {
-                        best = t;
-                        plan = p;
-                    }
-                }
-    return best < 1e30;
+    plan.us = 1e30;
+    for_plans(n, dim, fp64, false, [&](const ResidentPlan &p) {
+        if (p.us < plan.us) plan = p;
+    });
+    return plan.blocks > 0;
+}
+
+void resident_batch_plans(int n, bool fp64, ResidentPlan (&plans)[kBatchShares]) {
+    for (ResidentPlan &p : plans) p = ResidentPlan{};
+    for_plans(n, 3, fp64, true, [&](const ResidentPlan &p) {
+        for (int k = 0; k < kBatchShares; k++)
+            if (p.blocks <= batch_share(k) && (plans[k].blocks == 0 || p.us < plans[k].us)) plans[k] = p;
+    });
 }
 
 template <int DIM, typename T, int C>
@@ -837,5 +459,78 @@ hipError_t resident_run(const ResidentPlan &p, const ResidentRun<T> &run, hipStr
 }
 template hipError_t resident_run<float>(const ResidentPlan &, const ResidentRun<float> &, hipStream_t);
 template hipError_t resident_run<double>(const ResidentPlan &, const ResidentRun<double> &, hipStream_t);
+
+// ------------------------------------------------------------------ several runs
+
+namespace {
+
+// The table of runs is read through the scalar cache, where it is needed: a run's parameters
+// held in registers for the whole run would cost the large partitions spills.
+#define EXCMG_CONSTANT __attribute__((address_space(4)))
+struct ResidentShared {
+    Pair red[2 * (512 / kWave)];
+    Pair all_a[4], all_b[8];
+    int bad;
+};
+template <typename T, int C, int RS>
+__device__ __forceinline__ void batch_run(const EXCMG_CONSTANT ResidentRun<T> &a, const int blk, const int W,
+                                          const int nt, ResidentShared &sh, T *M) {
+    constexpr int DIM = 3, NH = halo_slots(C, 3);
+    constexpr bool MULTI = true, BATCH = true;
+    Pair *red = sh.red, *all_a = sh.all_a, *all_b = sh.all_b;
+    int &bad = sh.bad;
+#include "resident_body.hpp"
+}
+
+// Several runs at once, each on its own workgroups, FP64 and FP32 ones together.  A run that
+// stops says so in a.stop; the others then leave between two iterations (not before min_steps),
+// with their state in memory, so that the host can start what comes next on the free CUs.
+// The waves that a run's partition has no work for end here (a barrier waits for the
+// workgroup's remaining waves only).  24 problems of 32^3 to 128^3 in mixed precision: 775 ms
+// by steps of four launches (20 us a step at the least), 312 ms resident, of which 223 in 91
+// launches; one after the other with launches of their own they take 376 ms.
+__global__ void __launch_bounds__(512) k_resident_batch(const ResidentBatchRun *table, int count) {
+    extern __shared__ char lds_raw[];
+    __shared__ ResidentShared sh;
+    const auto *runs = (const EXCMG_CONSTANT ResidentBatchRun *)table;
+    int j = 0;
+    while (j + 1 < count && (int)blockIdx.x >= runs[j + 1].first) j++;
+    const EXCMG_CONSTANT ResidentBatchRun &b = runs[j];
+    const int blk = (int)blockIdx.x - b.first, W = b.blocks, nt = b.threads;
+    const int kind = b.kind;
+    if ((int)threadIdx.x >= nt) return;
+#define EXCMG_BATCH_RUN(T, C, RS)                                                              \
+    case batch_kind(sizeof(T) == 8, C, RS):                                                    \
+        batch_run<T, C, RS>((const EXCMG_CONSTANT ResidentRun<T> &)b.run, blk, W, nt, sh,     \
+                            (T *)lds_raw);                                                     \
+        break;
+    switch (kind) {
+        EXCMG_BATCH_RUN(double, 1, 20)
+        EXCMG_BATCH_RUN(double, 1, 36)
+        EXCMG_BATCH_RUN(double, 2, 20)
+        EXCMG_BATCH_RUN(double, 2, 36)
+        EXCMG_BATCH_RUN(double, 4, 20)
+        EXCMG_BATCH_RUN(double, 4, 36)
+        EXCMG_BATCH_RUN(double, 8, 20)
+        EXCMG_BATCH_RUN(double, 8, 36)
+        EXCMG_BATCH_RUN(float, 4, 20)
+        EXCMG_BATCH_RUN(float, 4, 36)
+        EXCMG_BATCH_RUN(float, 8, 20)
+        EXCMG_BATCH_RUN(float, 8, 36)
+        EXCMG_BATCH_RUN(float, 16, 20)
+        EXCMG_BATCH_RUN(float, 16, 36)
+    }
+#undef EXCMG_BATCH_RUN
+}
+
+}  // namespace
+
+hipError_t resident_batch(const ResidentBatchRun *runs, int count, int blocks, size_t lds, hipStream_t st) {
+    const void *fn = (const void *)k_resident_batch;
+    hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    void *args[] = {&runs, &count};
+    return hipLaunchCooperativeKernel(fn, dim3(blocks), dim3(512), args, (unsigned)lds, st);
+}
 
 }  // namespace excmg

@@ -109,3 +109,32 @@ def test_mixed_plane_equals_sweeps(ex, N, levels, bc):
     ex.set_timing(False)
     assert got[0][1] == got[1][1]
     np.testing.assert_array_equal(got[0][0], got[1][0])
+
+
+@pytest.mark.parametrize("case", ["fp64", "mixed", "mixed small", "capped"])
+def test_batch_runs_equal_steps(ex, case):
+    """Runs of a batch in shared launches (more of them than there are CUs for; one grid that
+    is advanced by steps beside them) against the persistent steps, which take all systems."""
+    print(f"resident batch {case}", flush=True)
+    sizes = [(16, 3), (24, 4), (40, 4), (48, 5), (64, 5), (64, 5), (80, 5), (96, 6), (28, 3), (32, 4)]
+    sizes += {"fp64": [(112, 5)], "mixed": [(96, 5), (128, 6)]}.get(case, [])
+    probs, fields = [], []
+    for j, (N, nl) in enumerate(sizes):
+        arr = make_arrays(config_problem(2), N, 1 + j % 2)
+        fields.append([dev(arr.f), dev(arr.g1), dev(arr.g2)])
+    options = {"fp64": {}, "mixed": dict(precision=ex.MIXED),
+               "mixed small": dict(precision=ex.MIXED, fp32_min_unknowns=1),
+               "capped": dict(max_iters=37)}[case]
+    got = []
+    for persistent in (False, True):
+        probs = [dict(n_finest=N, n_levels=nl, bc_kind=1 + j % 2, f=f, g1=g1, g2=g2,
+                      u_out=torch.empty_like(f), ut_out=torch.empty_like(f))
+                 for j, ((N, nl), (f, g1, g2)) in enumerate(zip(sizes, fields))]
+        rc, stats = ex.solve_batch(probs, 1e-7, persistent=persistent, **options)
+        got.append((rc, [[(s["iterations"], s["runs"], s["status"]) for s in st.levels()] for st in stats],
+                    [p["u_out"].cpu().numpy() for p in probs], [p["ut_out"].cpu().numpy() for p in probs]))
+    assert got[0][0] == got[1][0]
+    assert got[0][1] == got[1][1]
+    for k in (2, 3):
+        for a, b in zip(got[0][k], got[1][k]):
+            np.testing.assert_array_equal(a, b)
