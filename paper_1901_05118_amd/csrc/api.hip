@@ -737,7 +737,7 @@ int bicg_resident(const Level &L, double *x, BicgState &hs, bool *done) {
     const ResidentPlan &plan = c.resident(L, sizeof(T) == 8);
     if (plan.blocks == 0) return EXCMG_OK;
     const size_t cell_bytes = std::max((size_t)16, plan.exchange), slot_bytes = 6 * 256 * 16;
-    const unsigned steps = (unsigned)std::max(0, hs.maxit - hs.iter) + 2;
+    const unsigned steps = (unsigned)std::max(0, hs.maxit - hs.iter) + 3;
     const bool wrap = c.res_epoch + steps < c.res_epoch;
     if (wrap || c.res_cells.bytes < cell_bytes || c.res_slots.bytes < slot_bytes) {
         if (c.res_cells.ensure(cell_bytes) != EXCMG_OK || c.res_slots.ensure(slot_bytes) != EXCMG_OK) {
@@ -771,6 +771,7 @@ int bicg_resident(const Level &L, double *x, BicgState &hs, bool *done) {
     run.cells = c.res_cells.p;
     run.slots = c.res_slots.p;
     run.epoch = c.res_epoch;
+    run.one_xcd = plan.one_xcd;
     if (resident_run<T>(plan, run, g_stream) != hipSuccess) {
         (void)hipGetLastError();
         c.res_off = true;
@@ -795,7 +796,7 @@ int bicg_resident(const Level &L, double *x, BicgState &hs, bool *done) {
         CKH(hipStreamSynchronize(g_stream));
         return EXCMG_OK;
     }
-    c.res_epoch += (unsigned)(now.iter - iter0) + 2;
+    c.res_epoch += (unsigned)(now.iter - iter0) + 3;
     CKH((copy_convert<double, double>(L.nu, run.x_work, x, g_stream)));
     hs = now;
     *done = true;

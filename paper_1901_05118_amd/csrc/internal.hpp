@@ -220,6 +220,7 @@ struct ResidentPlan {
     int nbx = 0, nby = 0, nbz = 0, bx = 0, by = 0, bz = 0, C = 0, dim = 3;
     int rs = 0;                    // row stride of the LDS box
     int threads = 0, blocks = 0;
+    bool one_xcd = false;          // workgroups on one XCD, which exchange in its L2
     size_t lds = 0, exchange = 0;  // bytes of LDS; of exchanged cells
     double us = 0.0;               // modelled time of an iteration
 };
@@ -237,6 +238,7 @@ struct ResidentRun {
     void *cells;                   // exchanged cells (ResidentPlan::exchange bytes)
     void *slots;                   // exchanged partials: 6 planes of 16 bytes per workgroup (256)
     unsigned epoch;                // the run's exchanges are numbered from epoch + 1
+    bool one_xcd;                  // ResidentPlan::one_xcd
     // a run of a batch (r and r* are also written when it is halted; x_work may be x)
     unsigned min_steps, max_steps; // iterations before it may be, and is, halted
     unsigned *stop;                // the launch's: epoch + 1 once a run has stopped

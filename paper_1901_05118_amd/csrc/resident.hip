@@ -30,6 +30,13 @@
 // (at once: 32^3 6.1 -> 5.3 us, a look that comes too early costs another); the iterate in
 // registers, not in memory (96^3 32 -> 26 us).
 //
+// Small grids run on one XCD (at most 32 workgroups; where they are is found out by the
+// workgroups themselves): their stores end in the L2 that they share, and an all-to-all
+// exchange takes 1100 cycles instead of 3100.  16^3 5.9 -> 4.9 us, 128^2 4.7 -> 4.0; 32^3 as
+// fast either way (5.4 / 5.3: twice the cells per workgroup).  Every wave merging all partials
+// itself (no barrier, no way through LDS) was no faster: 4.9 -> 4.8 us on one XCD, 4.7 -> 5.0
+// past the L2s.
+//
 // Arithmetic: element for element that of the sweeps (zmarch.hpp, k_bicg_update), so the
 // iterates are the same; only the partition of the compensated sums differs, as it does
 // between launch shapes.
@@ -50,6 +57,7 @@ typedef unsigned long long u64;
 namespace {
 
 constexpr int kFirstLook = 24;              // s_sleep units (64 cycles)
+constexpr int kFirstLookL2 = 4;             // (on one XCD)
 constexpr u64 kWaitTicks = 200000000ull;    // 2 s of the 100 MHz constant clock
 
 // Exchanged memory is accessed 16 bytes at a time, at agent scope (sc1: past the L2 that the
@@ -68,10 +76,13 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t exchange_rsrc(void *p, unsigne
 __device__ __forceinline__ u32x4 get(__amdgpu_buffer_rsrc_t r, unsigned place, unsigned plane) {
     return __builtin_amdgcn_raw_buffer_load_b128(r, (int)place, (int)plane, kAgent);
 }
+// AUX: kAgent, or 0 between workgroups of one XCD (the store ends in the L2 they share, where
+// the reader's load, past its own L1, finds it).
+template <int AUX>
 __device__ __forceinline__ void put(__amdgpu_buffer_rsrc_t r, unsigned place, unsigned plane,
                                     unsigned a, unsigned b, unsigned ep) {
     const u32x4 w = {a, ep, b, ep};
-    __builtin_amdgcn_raw_buffer_store_b128(w, r, (int)place, (int)plane, kAgent);
+    __builtin_amdgcn_raw_buffer_store_b128(w, r, (int)place, (int)plane, AUX);
 }
 __device__ __forceinline__ bool is_new(u32x4 w, unsigned ep) { return w[1] == ep && w[3] == ep; }
 __device__ __forceinline__ unsigned low(double v) { return (unsigned)(u64)__double_as_longlong(v); }
@@ -82,14 +93,16 @@ __device__ __forceinline__ double as_double(u32x4 w) {
     return __longlong_as_double((long long)(((u64)w[2] << 32) | w[0]));
 }
 
-// r and r* of one cell in a mailbox: 8 or 16 bytes, at agent scope.
+// r and r* of one cell in a mailbox: 8 or 16 bytes.
+template <int AUX>
 __device__ __forceinline__ void put_cell(__amdgpu_buffer_rsrc_t x, unsigned cell, float r, float s) {
     const u32x2 w = {__float_as_uint(r), __float_as_uint(s)};
-    __builtin_amdgcn_raw_buffer_store_b64(w, x, (int)(8 * cell), 0, kAgent);
+    __builtin_amdgcn_raw_buffer_store_b64(w, x, (int)(8 * cell), 0, AUX);
 }
+template <int AUX>
 __device__ __forceinline__ void put_cell(__amdgpu_buffer_rsrc_t x, unsigned cell, double r, double s) {
     const u32x4 w = {low(r), high(r), low(s), high(s)};
-    __builtin_amdgcn_raw_buffer_store_b128(w, x, (int)(16 * cell), 0, kAgent);
+    __builtin_amdgcn_raw_buffer_store_b128(w, x, (int)(16 * cell), 0, AUX);
 }
 __device__ __forceinline__ void get_cell(__amdgpu_buffer_rsrc_t x, unsigned cell, float &r, float &s) {
     const u32x2 w = __builtin_amdgcn_raw_buffer_load_b64(x, (int)(8 * cell), 0, kAgent);
@@ -187,6 +200,24 @@ __device__ __forceinline__ Pair gather_pairs(__amdgpu_buffer_rsrc_t slots, unsig
     wave_merge_n<1>(v);
     return v[0];
 }
+
+// Whether all of up to 64 workgroups sent this value.
+__device__ __forceinline__ bool gather_same(__amdgpu_buffer_rsrc_t slots, unsigned place,
+                                            unsigned plane, unsigned ep, unsigned value, int *bad) {
+    const u64 t0 = wall_clock64();
+    for (;;) {
+        asm volatile("" ::: "memory");
+        const u32x4 s = get(slots, place, plane);
+        if (__all(is_new(s, ep) || place == kNoPlace)) return __all(s[0] == value || place == kNoPlace);
+        if (wall_clock64() - t0 > kWaitTicks) {
+            *bad = 1;
+            return false;
+        }
+    }
+}
+
+// The XCD that this workgroup runs on (hardware register XCC_ID, 4 bits).
+__device__ __forceinline__ unsigned xcd_id() { return __builtin_amdgcn_s_getreg((3 << 11) | 20); }
 
 // The 25-point sums of C consecutive outputs of one column.  B points two rows, two cells and
 // two planes below output 0 in LDS (row stride RS, plane stride ps), so that every read of a
@@ -313,7 +344,11 @@ __global__ void __launch_bounds__(MT) k_resident(ResidentRun<T> a) {
     __shared__ int bad;
     T *M = (T *)lds_raw;
     constexpr bool BATCH = false;
-    const int blk = MULTI ? blockIdx.x : 0, W = MULTI ? gridDim.x : 1, nt = blockDim.x;
+    // one XCD: the launch has 8 times the workgroups, which the XCDs take in turn
+    const bool one_xcd = MULTI && C <= 8 && a.one_xcd;
+    if (one_xcd && (blockIdx.x & 7)) return;
+    const int blk = !MULTI ? 0 : one_xcd ? blockIdx.x >> 3 : blockIdx.x;
+    const int W = !MULTI ? 1 : one_xcd ? gridDim.x >> 3 : gridDim.x, nt = blockDim.x;
 #include "resident_body.hpp"
 }
 
@@ -324,8 +359,8 @@ hipError_t launch_resident(const ResidentPlan &pl, ResidentRun<T> run, hipStream
     hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)pl.lds);
     if (e != hipSuccess) return e;
     void *args[] = {&run};
-    return hipLaunchCooperativeKernel(fn, dim3(pl.blocks), dim3(pl.threads), args,
-                                      (unsigned)pl.lds, st);
+    return hipLaunchCooperativeKernel(fn, dim3(run.one_xcd ? 8 * pl.blocks : pl.blocks),
+                                      dim3(pl.threads), args, (unsigned)pl.lds, st);
 }
 
 // Halo cells per thread and largest workgroup of the kernel with C cells per thread (what
@@ -338,6 +373,7 @@ constexpr int max_threads(int C, bool fp64, int dim) {
 constexpr int max_batch_threads(int C, bool fp64) {
     return C == 16 && fp64 ? 0 : C <= 2 && !fp64 ? 0 : 512;
 }
+constexpr int kXcdGroups = 32;              // CUs of an XCD
 constexpr size_t kMaxLds = 158 * 1024;     // of 160 KB per workgroup; the rest is static
 
 // Partition of the grid into nbx x nby x nbz bricks (2D: rows are z, nby = 1) with C cells
@@ -397,6 +433,12 @@ void for_plans(int n, int dim, bool fp64, bool batch, Use use) {
                         p.us += 0.83 + 0.094 * W / 64 + 0.32 * ((p.blocks + 63) / 64) +
                                 0.048 * waves * halo_slots(C, dim) +
                                 2.1e-7 * (double)p.exchange * (fp64 ? 1 : 2);
+                    // fewer workgroups, on one XCD (the kernels with 16 cells have no
+                    // register for the choice)
+                    if (!batch && C <= 8 && p.blocks > 1 && p.blocks <= kXcdGroups) {
+                        p.one_xcd = true;
+                        p.us -= 0.85;
+                    }
                     use(p);
                 }
 }
@@ -407,9 +449,9 @@ void for_plans(int n, int dim, bool fp64, bool batch, Use use) {
 // (us), fitted to some 5000 partitions of 3D grids of 12 to 96 cells (FP64; what it picks takes
 // 0-12% longer than the best of each grid): work per wave and per thread, exchanges that grow
 // with the number of workgroups, cells exchanged.  Measured per iteration against the
-// launch-per-sweep form: 16^3 5.3 / 17.9, 32^3 5.4 / 18.3, 48^3 7.7 / 21.3, 64^3 10.0 / 26.1,
+// launch-per-sweep form: 16^3 4.9 / 17.9, 32^3 5.3 / 18.3, 48^3 7.7 / 21.3, 64^3 10.0 / 26.1,
 // 96^3 16.5 / 45.0 us.  FP32 vectors: 96^3 13.4 / 37.3, 112^3 20.1 / 48.9, 128^3 (8192 cells
-// per workgroup, 16 per thread) 22 / 45.  Planes, FP64: 128^2 4.7 / 12.1, 256^2 5.0 / 13.3,
+// per workgroup, 16 per thread) 22 / 45.  Planes, FP64: 128^2 4.0 / 12.1, 256^2 5.0 / 13.3,
 // 512^2 7.3 / 24.2, 1024^2 (whole run of 15) 24 / 64.
 // FP64 grids above about 100^3 do not fit (16 cells of six FP64 vectors and the halo take more
 // than the 256 registers of 512 threads), nor do planes above about 1000^2; smaller grids are

@@ -163,6 +163,25 @@
         }
     }
     unsigned ep = a.epoch, halted = 0;
+    // Workgroups launched for one XCD tell each other where they are (past the L2s, in the
+    // plane of rho', which is next written after an exchange that needs them all).
+    bool l2 = false;
+    if constexpr (MULTI && !BATCH && C <= 8) {
+        if (a.one_xcd) {
+            ep++;
+            const unsigned xcd = xcd_id();
+            if (tid < 64) {
+                if (tid == 0) put<kAgent>(xs, 16u * (unsigned)blk, 2 * kSlotPlane, xcd, 0, ep);
+                const bool same = gather_same(xs, tid < W ? 16u * (unsigned)tid : kNoPlace,
+                                              2 * kSlotPlane, ep, xcd, &bad);
+                if (tid == 0) all_a[0].s = same ? 1.0 : 0.0;
+            }
+            __syncthreads();
+            l2 = __builtin_amdgcn_readfirstlane(all_a[0].s != 0.0);
+            __syncthreads();
+            if (bad) status = kStopping;    // (no iteration; the host sees err)
+        }
+    }
     // Phases of an iteration are kept apart in the registers: addresses and FP64 forms of FP32
     // values that one phase derives are not carried into the next.
     auto keep = [&]() {
@@ -237,7 +256,9 @@
             if (MULTI) {
                 if (lane < 2) {
                     const double b = lane == 0 ? v[0].s : v[0].c;
-                    put(xs, 16u * (unsigned)blk + lane * kSlotPlane, 0, low(b), high(b), ep);
+                    const unsigned at = 16u * (unsigned)blk + lane * kSlotPlane;
+                    if (l2) put<0>(xs, at, 0, low(b), high(b), ep);
+                    else put<kAgent>(xs, at, 0, low(b), high(b), ep);
                 }
             } else if (lane == 0) {
                 all_a[0] = v[0];
@@ -312,7 +333,8 @@
 #pragma unroll
             for (int q = 0; q < NH; q++) {
                 const int src = (unsigned)hplace[q] >> 16;
-                put_cell(xc, hdest[q], R[src], R[own + src]);
+                if (l2) put_cell<0>(xc, hdest[q], R[src], R[own + src]);
+                else put_cell<kAgent>(xc, hdest[q], R[src], R[own + src]);
             }
         }
         keep();
@@ -344,7 +366,9 @@
                 if (lane < 4) {
                     const Pair pv = lane < 2 ? v[0] : v[1];
                     const double b = (lane & 1) ? pv.c : pv.s;
-                    put(xs, 16u * (unsigned)blk + (2 + lane) * kSlotPlane, 0, low(b), high(b), ep);
+                    const unsigned at = 16u * (unsigned)blk + (2 + lane) * kSlotPlane;
+                    if (l2) put<0>(xs, at, 0, low(b), high(b), ep);
+                    else put<kAgent>(xs, at, 0, low(b), high(b), ep);
                 }
             } else if (lane == 0) {
                 all_b[0] = v[0];
@@ -353,7 +377,8 @@
         }
         if (MULTI) {
             // A load takes about 1800 cycles (past the L2); asked too early it is asked twice.
-            __builtin_amdgcn_s_sleep(kFirstLook);
+            if (l2) __builtin_amdgcn_s_sleep(kFirstLookL2);
+            else __builtin_amdgcn_s_sleep(kFirstLook);
             if (64 * (wave >> 1) < W) {     // even waves: rho', odd waves: r.r
                 const int w = (wave >> 1) * 64 + lane;
                 const Pair v = gather_pairs(xs, w < W ? 16u * (unsigned)w : kNoPlace,
