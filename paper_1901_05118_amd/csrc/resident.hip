@@ -115,6 +115,26 @@ __device__ __forceinline__ void get_cell(__amdgpu_buffer_rsrc_t x, unsigned cell
     s = __longlong_as_double((long long)(((u64)w[3] << 32) | w[2]));
 }
 
+// One FP64 value of a mailbox.
+__device__ __forceinline__ void put_value(__amdgpu_buffer_rsrc_t x, unsigned cell, double v) {
+    const u32x2 w = {low(v), high(v)};
+    __builtin_amdgcn_raw_buffer_store_b64(w, x, (int)(8 * cell), 0, kAgent);
+}
+__device__ __forceinline__ double get_value(__amdgpu_buffer_rsrc_t x, unsigned cell) {
+    const u32x2 w = __builtin_amdgcn_raw_buffer_load_b64(x, (int)(8 * cell), 0, kAgent);
+    return __longlong_as_double((long long)(((u64)w[1] << 32) | w[0]));
+}
+
+// One FP64 value of this workgroup's own (no value past the end).
+__device__ __forceinline__ double load_f64(__amdgpu_buffer_rsrc_t x, unsigned i) {
+    const u32x2 w = __builtin_amdgcn_raw_buffer_load_b64(x, (int)(8 * i), 0, 0);
+    return __longlong_as_double((long long)(((u64)w[1] << 32) | w[0]));
+}
+__device__ __forceinline__ void store_f64(__amdgpu_buffer_rsrc_t x, unsigned i, double v) {
+    const u32x2 w = {low(v), high(v)};
+    __builtin_amdgcn_raw_buffer_store_b64(w, x, (int)(8 * i), 0, 0);
+}
+
 // v of the lane that a DPP control pairs with this one.
 template <int CTRL>
 __device__ __forceinline__ double dpp_double(double v) {
@@ -364,10 +384,10 @@ hipError_t launch_resident(const ResidentPlan &pl, ResidentRun<T> run, hipStream
 }
 
 // Halo cells per thread and largest workgroup of the kernel with C cells per thread (what
-// its registers hold without spilling; 16 cells: FP32 in 3D only).
+// its registers hold; 16 cells: in 3D only).
 constexpr int halo_slots(int C, int dim) { return dim == 2 ? 2 : C <= 2 ? 4 : C == 4 ? 6 : C == 8 ? 8 : 11; }
 constexpr int max_threads(int C, bool fp64, int dim) {
-    return C == 16 && (fp64 || dim == 2) ? 0 : C <= 2 && !fp64 ? 1024 : 512;
+    return C == 16 && dim == 2 ? 0 : C <= 2 && !fp64 ? 1024 : 512;
 }
 // (a run of a batch: FP32 with at least 4 cells per thread)
 constexpr int max_batch_threads(int C, bool fp64) {
@@ -408,7 +428,9 @@ bool try_plan(int n, int dim, bool fp64, bool batch, int nbx, int nby, int nbz, 
     const size_t es = fp64 ? 8 : 4;
     p.rs = p.bx <= 16 && dim == 3 ? 20 : 36;
     p.lds = ((size_t)p.rs * (dim == 2 ? 1 : p.by + 4) * (groups * C + 4) + 1) * es;
-    if (!one) p.lds += 2 * (size_t)columns * C * es;
+    const bool lean = fp64 && C == 16;
+    if (lean && one) return false;
+    if (!one) p.lds += (lean ? (size_t)p.bx * p.by : 2 * (size_t)columns) * C * es;
     p.exchange = one ? 0 : (size_t)p.blocks * halo * 2 * es;
     return p.lds <= kMaxLds;
 }
@@ -428,7 +450,8 @@ void for_plans(int n, int dim, bool fp64, bool batch, Use use) {
                     if (!whole(bz) || !whole(bx) || (dim == 3 && !whole(by))) continue;
                     if (!try_plan(n, dim, fp64, batch, bx, by, bz, C, p)) continue;
                     const double waves = p.threads / 64, W = p.blocks;
-                    p.us = 0.056 * waves * C + 0.086 * waves + 0.36 * C;
+                    p.us = fp64 && C == 16 ? 8.0 : 0.0;     // (the iterate in memory)
+                    p.us += 0.056 * waves * C + 0.086 * waves + 0.36 * C;
                     if (p.blocks > 1)
                         p.us += 0.83 + 0.094 * W / 64 + 0.32 * ((p.blocks + 63) / 64) +
                                 0.048 * waves * halo_slots(C, dim) +
@@ -453,8 +476,9 @@ void for_plans(int n, int dim, bool fp64, bool batch, Use use) {
 // 96^3 16.5 / 45.0 us.  FP32 vectors: 96^3 13.4 / 37.3, 112^3 20.1 / 48.9, 128^3 (8192 cells
 // per workgroup, 16 per thread) 22 / 45.  Planes, FP64: 128^2 4.0 / 12.1, 256^2 5.0 / 13.3,
 // 512^2 7.3 / 24.2, 1024^2 (whole run of 15) 24 / 64.
-// FP64 grids above about 100^3 do not fit (16 cells of six FP64 vectors and the halo take more
-// than the 256 registers of 512 threads), nor do planes above about 1000^2; smaller grids are
+// FP64 with 16 cells per thread (112^3, 128^3): 32.9 / 46.9, 37.5 / 51.4; half of it is what
+// goes past the L2 (the iterate, 33 MB an iteration, and the halo, 44 MB, at about 4.5 TB/s),
+// and it still spills 38 registers.  Planes above about 1000^2 do not fit; smaller grids are
 // levels solved directly.
 bool resident_plan(int n, int dim, bool fp64, ResidentPlan &plan) {
     plan.us = 1e30;

@@ -3,6 +3,11 @@
 // thread; MULTI: more than one brick; BATCH: one of several runs of a launch, which may be
 // halted between two iterations.  Included where it is compiled: called as a function, the
 // kernel with 16 cells per thread needs 11 more registers than there are.
+    // FP64 with 16 cells per thread: what does not fit is left out of the registers.  The
+    // iterate is in memory; q* is not kept (alpha is waited for before it is formed, and r* takes
+    // it term by term); phases go through the cells G at a time; r and r* are sent in parts.
+    constexpr bool kLean = sizeof(T) == 8 && C == 16;
+    constexpr int G = kLean ? 4 : C;
     int tid = threadIdx.x;
     const int nw = nt >> 6;
     const int n = a.n, bx = a.bx, by = a.by, bz = a.bz;
@@ -32,7 +37,7 @@
     int cells = (lg < groups && gx < n && gy < ny) ? max(0, min(C, min(n, z0 + bz) - gz)) : 0;
     int ob = ((min(lg, groups - 1) * C + 2) * (by + 2 * HY) + ly + HY) * BX + lx + 2;
     int gi = cells > 0 ? (gz * ny + gy) * n + gx : 0;
-    const int gplane = cells > 0 ? ny * n : 0;
+    const int gplane = kLean || cells > 0 ? ny * n : 0;
     // fictitious points that mirror this column
     const int ghx = cells == 0 ? 0 : gx == 0 ? -2 : (gx == n - 1 ? 2 : 0);
     const int ghy = cells == 0 || DIM == 2 ? 0 : gy == 0 ? -2 * BX : (gy == n - 1 ? 2 * BX : 0);
@@ -44,9 +49,11 @@
     const int hn = DIM == 3 ? 4 * (bx * by + bx * bz + by * bz + bx + by + bz) : 4 * (bx + bz + 1);
     const __amdgpu_buffer_rsrc_t xc = exchange_rsrc(a.cells, 2u * sizeof(T) * (unsigned)(W * hn)),
                                  xs = exchange_rsrc(a.slots, 6 * kSlotPlane);
+    [[maybe_unused]] const __amdgpu_buffer_rsrc_t xw =
+        exchange_rsrc(a.x_work, kLean ? 8u * (unsigned)(n * n * n) : 0u);
     const int own = bx * by * groups * C;     // staged r and r* of the brick: R, R + own
     T *R = M + LE + 1;
-    const int os = cells > 0 ? (lg * C * by + ly) * bx + lx : 0, oplane = bx * by;
+    int os = cells > 0 ? (lg * C * by + ly) * bx + lx : 0, oplane = bx * by;
     int hplace[MULTI ? NH : 1];               // place in LDS (LE: none) | staged source << 16
     unsigned hdest[MULTI ? NH : 1];           // cell of a neighbour's box (kNoCell: none)
     T hr[MULTI ? NH : 1], hs[MULTI ? NH : 1], hv[MULTI ? NH : 1];  // r, r*, the direction not in LDS
@@ -81,18 +88,19 @@
     }
     auto hoff = [&](int q) { return hplace[q] & 0xffff; };
 
-    // own values into LDS, and into the fictitious points that mirror them
+    // own values c0 .. c0 + G - 1 into LDS, and into the fictitious points that mirror them
     const bool edge = ghx || ghy || ghz0 || ghz1;
-    auto place = [&](const T (&v)[C]) {
+    auto place = [&](const int c0, const T (&v)[G]) {
 #pragma unroll
-        for (int c = 0; c < C; c++) M[c < cells ? ob + c * PS : LE] = v[c];
+        for (int k = 0; k < G; k++) M[c0 + k < cells ? ob + (c0 + k) * PS : LE] = v[k];
         if (edge) {
             const bool neg = a.sgn < 0;
 #pragma unroll
-            for (int c = 0; c < C; c++) {
+            for (int k = 0; k < G; k++) {
+                const int c = c0 + k;
                 if (c < cells) {
                     T *P = M + ob + c * PS;
-                    const T g = neg ? -v[c] : v[c];
+                    const T g = neg ? -v[k] : v[k];
                     if (ghx) P[ghx] = g;
                     if (ghy) P[ghy] = g;
                     if (c == 0 && ghz0) P[-2 * PS] = g;
@@ -127,18 +135,19 @@
     // In the first iteration of a run p = r and p* = r*: the old directions are zeros and
     // beta is 0.
     T r[C], s[C], o[C];      // r, r*, and p while LDS holds p* (p* while it holds p)
-    double xv[C];            // the iterate
+    double xv[kLean ? 1 : C];   // the iterate
     {
         const T *p = a.p[iter & 1], *ps = a.ps[iter & 1];
 #pragma unroll
         for (int c = 0; c < C; c++) {
             r[c] = s[c] = o[c] = (T)0;
-            xv[c] = 0.0;
+            if (!kLean) xv[kLean ? 0 : c] = 0.0;
             if (c < cells) {
                 const unsigned i = gi + c * gplane;
                 r[c] = a.r[i];
                 s[c] = a.rs[i];
-                xv[c] = a.x[i];
+                if (kLean) a.x_work[i] = a.x[i];
+                else xv[kLean ? 0 : c] = a.x[i];
                 if (!first) {
                     o[c] = p[i];
                     M[ob + c * PS] = ps[i];
@@ -186,7 +195,8 @@
     // values that one phase derives are not carried into the next.
     auto keep = [&]() {
         asm volatile("" : "+v"(ob), "+v"(cells));
-        if constexpr (sizeof(T) == 4) {
+        if constexpr (kLean) asm volatile("" : "+v"(gi), "+v"(os), "+v"(tid));
+        if constexpr (sizeof(T) == 4 || kLean) {
 #pragma unroll
             for (int c = 0; c < C; c++) asm volatile("" : "+v"(r[c]), "+v"(s[c]), "+v"(o[c]));
         }
@@ -202,6 +212,27 @@
         else column_outputs_2d<C, T>(B, PS, emit);
     };
 
+    // (lean) One of r and r* of the cells that others read, the threads of one z-group at a time.
+    [[maybe_unused]] auto send = [&](const T (&v)[C], const unsigned box) {
+        const int part = own / groups;
+        for (int g = 0; g < groups; g++) {
+            keep();
+            if (lg == g && cells > 0) {    // (cells past the grid have their place, too)
+                T *to = R + (os - g * part);
+#pragma unroll
+                for (int c = 0; c < C; c++) to[c * oplane] = v[c];
+            }
+            __syncthreads();
+#pragma unroll
+            for (int q = 0; q < NH; q++) {
+                const int src = (int)((unsigned)hplace[q] >> 16) - g * part;
+                const bool here = hdest[q] != kNoCell && src >= 0 && src < part;
+                put_value(xc, here ? box + hdest[q] : kNoCell, R[here ? src : 0]);
+            }
+            __syncthreads();
+        }
+    };
+
     while (status == kRunning) {
         ep++;
         asm volatile("" : "+v"(tid));
@@ -213,22 +244,34 @@
         keep();
         // ---- directions: p into LDS, p* into o and hv
         T ho[MULTI ? NH : 1];
-        {
-            T pn[C], so[C];
+        if constexpr (kLean) {
 #pragma unroll
-            for (int c = 0; c < C; c++) so[c] = M[ob + c * PS];
-            if (MULTI) {
+            for (int q = 0; q < NH; q++) {
+                const T h = M[hoff(q)];
+                M[hoff(q)] = (T)((double)hr[q] + beta * (double)hv[q]);
+                hv[q] = (T)((double)hs[q] + beta * (double)h);
+            }
+            keep();
+        }
+#pragma unroll
+        for (int c0 = 0; c0 < C; c0 += G) {
+            T pn[G], so[G];
+#pragma unroll
+            for (int k = 0; k < G; k++) so[k] = M[ob + (c0 + k) * PS];
+            if (MULTI && !kLean) {
 #pragma unroll
                 for (int q = 0; q < NH; q++) ho[q] = M[hoff(q)];
             }
 #pragma unroll
-            for (int c = 0; c < C; c++) {
-                pn[c] = (T)((double)r[c] + beta * (double)o[c]);
-                o[c] = (T)((double)s[c] + beta * (c < cells ? (double)so[c] : 0.0));
+            for (int k = 0; k < G; k++) {
+                const int c = c0 + k;
+                pn[k] = (T)((double)r[c] + beta * (double)o[c]);
+                o[c] = (T)((double)s[c] + beta * (c < cells ? (double)so[k] : 0.0));
             }
-            place(pn);
+            place(c0, pn);
+            if (kLean) keep();
         }
-        if (MULTI) {
+        if (MULTI && !kLean) {
 #pragma unroll
             for (int q = 0; q < NH; q++)
                 M[hoff(q)] = (T)((double)hr[q] + beta * (double)hv[q]);
@@ -239,13 +282,13 @@
         keep();
 
         // ---- q = A p, sigma = p*.q
-        T qv[C], qs[C];
+        T qv[C], qs[kLean ? 1 : C];
         Pair sg[1] = {{0.0, 0.0}};
         stencil([&](int c, double y) {
             qv[c] = c < cells ? (T)y : (T)0;
             dot2_acc(sg[0], (double)o[c], (double)qv[c]);
             // (one output after the other)
-            if (C >= 8) asm volatile("" : "+v"(sg[0].s), "+v"(sg[0].c), "+v"(qv[c]));
+            if (C >= 8) asm volatile("" : "+v"(sg[0].s), "+v"(sg[0].c), "+v"(qv[c])); if (kLean) asm volatile("" ::: "memory");
         });
         wave_merge_n<1>(sg);
         if (lane == 0) red[wave] = sg[0];
@@ -266,34 +309,40 @@
         }
         // ---- p* into LDS, p into o and hv; q* = A^T p*
         keep();
-        {
-            T pv[C];
 #pragma unroll
-            for (int c = 0; c < C; c++) pv[c] = M[ob + c * PS];
-            if (MULTI) {
+        for (int c0 = 0; c0 < C; c0 += G) {
+            T pv[G], po[G];
+#pragma unroll
+            for (int k = 0; k < G; k++) pv[k] = M[ob + (c0 + k) * PS];
+            if (MULTI && c0 == 0) {
 #pragma unroll
                 for (int q = 0; q < NH; q++) ho[q] = M[hoff(q)];
             }
-            place(o);
 #pragma unroll
-            for (int c = 0; c < C; c++) o[c] = c < cells ? pv[c] : (T)0;
-        }
-        if (MULTI) {
+            for (int k = 0; k < G; k++) po[k] = o[c0 + k];
+            place(c0, po);
 #pragma unroll
-            for (int q = 0; q < NH; q++) {
-                M[hoff(q)] = hv[q];
-                hv[q] = ho[q];
+            for (int k = 0; k < G; k++) o[c0 + k] = c0 + k < cells ? pv[k] : (T)0;
+            if (MULTI && c0 == 0) {
+#pragma unroll
+                for (int q = 0; q < NH; q++) {
+                    M[hoff(q)] = hv[q];
+                    hv[q] = ho[q];
+                }
             }
+            if (kLean) keep();
         }
         __syncthreads();
         keep();
-        stencil([&](int c, double y) {
-            qs[c] = c < cells ? (T)y : (T)0;
-            if (C >= 8) asm volatile("" : "+v"(qs[c]));
-        });
-        // (q* is formed here, before the wait, not carried over it as its 21 C terms)
+        if constexpr (!kLean) {
+            stencil([&](int c, double y) {
+                qs[c] = c < cells ? (T)y : (T)0;
+                if (C >= 8) asm volatile("" : "+v"(qs[c]));
+            });
+            // (q* is formed here, before the wait, not carried over it as its 21 C terms)
 #pragma unroll
-        for (int c = 0; c < C; c++) asm volatile("" : "+v"(qs[c]));
+            for (int c = 0; c < C; c++) asm volatile("" : "+v"(qs[c]));
+        }
 
         // ---- sigma and alpha
         if (MULTI) {
@@ -319,16 +368,30 @@
         keep();
         // ---- r -= alpha q, r* -= alpha q*; rho' = r*.r and r.r; x += alpha p
         Pair dt[2] = {{0.0, 0.0}, {0.0, 0.0}};
+        if constexpr (kLean) {
 #pragma unroll
-        for (int c = 0; c < C; c++) {
-            r[c] = (T)((double)r[c] - alpha * (double)qv[c]);
-            s[c] = (T)((double)s[c] - alpha * (double)qs[c]);
-            if (MULTI && c < cells) {
-                R[os + c * oplane] = r[c];
-                R[own + os + c * oplane] = s[c];
+            for (int c = 0; c < C; c++) {
+                r[c] = (T)((double)r[c] - alpha * (double)qv[c]);
+                asm volatile("" : "+v"(r[c]));
+            }
+            send(r, 0u);
+            stencil([&](int c, double y) {
+                s[c] = (T)((double)s[c] - alpha * (c < cells ? y : 0.0));
+                asm volatile("" : "+v"(s[c]) :: "memory");
+            });
+            send(s, (unsigned)(W * hn));
+        } else {
+#pragma unroll
+            for (int c = 0; c < C; c++) {
+                r[c] = (T)((double)r[c] - alpha * (double)qv[c]);
+                s[c] = (T)((double)s[c] - alpha * (double)qs[kLean ? 0 : c]);
+                if (MULTI && c < cells) {
+                    R[os + c * oplane] = r[c];
+                    R[own + os + c * oplane] = s[c];
+                }
             }
         }
-        if (MULTI) {
+        if (MULTI && !kLean) {
             __syncthreads();
 #pragma unroll
             for (int q = 0; q < NH; q++) {
@@ -342,7 +405,7 @@
         for (int c = 0; c < C; c++) {
             dot2_acc(dt[0], (double)s[c], (double)r[c]);
             dot2_acc(dt[1], (double)r[c], (double)r[c]);
-            xv[c] = xv[c] + alpha * (double)o[c];
+            if (!kLean) xv[kLean ? 0 : c] = xv[kLean ? 0 : c] + alpha * (double)o[c];
         }
         wave_merge_n<2>(dt);
         if (lane == 0) {
@@ -375,10 +438,27 @@
                 all_b[1] = v[1];
             }
         }
+        // (while the partials travel)
+        if constexpr (kLean) {
+            constexpr int GX = 8;
+#pragma unroll
+            for (int c0 = 0; c0 < C; c0 += GX) {
+                double xv[GX];
+                unsigned at[GX];
+#pragma unroll
+                for (int k = 0; k < GX; k++) {
+                    at[k] = c0 + k < cells ? (unsigned)(gi + (c0 + k) * gplane) : kNoCell;
+                    xv[k] = load_f64(xw, at[k]);
+                }
+#pragma unroll
+                for (int k = 0; k < GX; k++) store_f64(xw, at[k], xv[k] + alpha * (double)o[c0 + k]);
+                asm volatile("" ::: "memory");
+            }
+        }
         if (MULTI) {
             // A load takes about 1800 cycles (past the L2); asked too early it is asked twice.
             if (l2) __builtin_amdgcn_s_sleep(kFirstLookL2);
-            else __builtin_amdgcn_s_sleep(kFirstLook);
+            else if (!kLean) __builtin_amdgcn_s_sleep(kFirstLook);
             if (64 * (wave >> 1) < W) {     // even waves: rho', odd waves: r.r
                 const int w = (wave >> 1) * 64 + lane;
                 const Pair v = gather_pairs(xs, w < W ? 16u * (unsigned)w : kNoPlace,
@@ -390,7 +470,14 @@
             // that the grid does not have reads as anything and goes nowhere)
             unsigned cell = (unsigned)(blk * hn + tid);
 #pragma unroll
-            for (int q = 0; q < NH; q++, cell += nt) get_cell(xc, cell, hr[q], hs[q]);
+            for (int q = 0; q < NH; q++, cell += nt) {
+                if constexpr (kLean) {
+                    hr[q] = get_value(xc, cell);
+                    hs[q] = get_value(xc, (unsigned)(W * hn) + cell);
+                } else {
+                    get_cell(xc, cell, hr[q], hs[q]);
+                }
+            }
             if (BATCH) halted = __hip_atomic_load(a.halt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         } else {
             __syncthreads();
@@ -428,7 +515,7 @@
         for (int c = 0; c < C; c++) {
             if (c < cells) {
                 const unsigned i = gi + c * gplane;
-                a.x_work[i] = xv[c];
+                if (!kLean) a.x_work[i] = xv[kLean ? 0 : c];
                 p[i] = o[c];
                 ps[i] = M[ob + c * PS];
                 if (BATCH && status == kRunning) {

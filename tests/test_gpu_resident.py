@@ -31,7 +31,7 @@ def dev(a):
     return torch.from_numpy(np.ascontiguousarray(a, dtype=np.float64)).cuda()
 
 
-# (cells, levels): 8^3 and 10^3 are the smallest grids the form takes, 96^3 the largest in FP64
+# (cells, levels): 8^3 and 10^3 are the smallest grids the form takes
 @pytest.mark.parametrize("N,levels", [(8, 3), (12, 3), (16, 3), (20, 3), (28, 3), (40, 4), (48, 5),
                                       (56, 4), (80, 5), (96, 6)])
 @pytest.mark.parametrize("bc", [1, 2])
@@ -138,3 +138,20 @@ def test_batch_runs_equal_steps(ex, case):
     for k in (2, 3):
         for a, b in zip(got[0][k], got[1][k]):
             np.testing.assert_array_equal(a, b)
+
+
+# FP64 with 16 cells per thread (the iterate in memory, q* not kept)
+@pytest.mark.parametrize("N,levels", [(112, 5), (128, 6)])
+@pytest.mark.parametrize("bc", [1, 2])
+def test_large_run_equals_oracle(ex, N, levels, bc):
+    print(f"resident N={N} bc={bc}", flush=True)
+    ex.setup(N, levels, bc)
+    rng = np.random.default_rng(N + bc)
+    b, x0 = rng.standard_normal((2, (N - 1) ** 3))
+    for its in (1, 9):
+        x = dev(x0)
+        rc, it, rr = ex.bicg(levels - 1, dev(b), x, 0.0, its)
+        xr, itr, rrr, rcr = O.bicg(N, bc, b, x0, 0.0, maxit=its)
+        assert rc == ex.ENOCONV and it == itr == its
+        assert rr == rrr
+        np.testing.assert_array_equal(x.cpu().numpy(), xr)
