@@ -451,16 +451,19 @@ void for_plans(int n, int dim, bool fp64, bool batch, Use use) {
                     if (!try_plan(n, dim, fp64, batch, bx, by, bz, C, p)) continue;
                     const double waves = p.threads / 64, W = p.blocks;
                     p.us = fp64 && C == 16 ? 8.0 : 0.0;     // (the iterate in memory)
-                    p.us += 0.056 * waves * C + 0.086 * waves + 0.36 * C;
+                    // (rows of other lengths leave LDS banks idle; a cell of the plane has half
+                    // the terms)
+                    const double cell = 0.0214 + (p.bx % 4 ? 0.0256 : 0.0) + (p.bx % 16 ? 0.0134 : 0.0);
+                    p.us += (dim == 2 ? 0.5 : 1.0) * (cell * waves * C + 0.559 * C) + 0.277 * waves;
                     if (p.blocks > 1)
-                        p.us += 0.83 + 0.094 * W / 64 + 0.32 * ((p.blocks + 63) / 64) +
-                                0.048 * waves * halo_slots(C, dim) +
-                                2.1e-7 * (double)p.exchange * (fp64 ? 1 : 2);
+                        p.us += 2.53 + 0.1225 * W / 64 + 0.0853 * ((p.blocks + 63) / 64) +
+                                0.005 * waves * halo_slots(C, dim) +
+                                6.5e-6 * (double)p.exchange / (fp64 ? 16 : 8);
                     // fewer workgroups, on one XCD (the kernels with 16 cells have no
                     // register for the choice)
                     if (!batch && C <= 8 && p.blocks > 1 && p.blocks <= kXcdGroups) {
                         p.one_xcd = true;
-                        p.us -= 0.85;
+                        p.us -= 0.514;
                     }
                     use(p);
                 }
@@ -469,13 +472,13 @@ void for_plans(int n, int dim, bool fp64, bool batch, Use use) {
 }  // namespace
 
 // The partition of an n^3 grid or n^2 plane: the cheapest by a model of an iteration's time
-// (us), fitted to some 5000 partitions of 3D grids of 12 to 96 cells (FP64; what it picks takes
-// 0-12% longer than the best of each grid): work per wave and per thread, exchanges that grow
-// with the number of workgroups, cells exchanged.  Measured per iteration against the
-// launch-per-sweep form: 16^3 4.9 / 17.9, 32^3 5.3 / 18.3, 48^3 7.7 / 21.3, 64^3 10.0 / 26.1,
+// (us), fitted to 800 partitions of 3D grids of 12 to 96 cells (FP64; what it picks takes 3%
+// longer than the best of each grid, 9% at most): work per wave and per thread, exchanges that
+// grow with the number of workgroups, cells exchanged.  Measured per iteration against the
+// launch-per-sweep form: 16^3 4.7 / 17.9, 32^3 5.2 / 18.3, 48^3 7.1 / 21.3, 64^3 9.7 / 26.1,
 // 96^3 16.5 / 45.0 us.  FP32 vectors: 96^3 13.4 / 37.3, 112^3 20.1 / 48.9, 128^3 (8192 cells
-// per workgroup, 16 per thread) 22 / 45.  Planes, FP64: 128^2 4.0 / 12.1, 256^2 5.0 / 13.3,
-// 512^2 7.3 / 24.2, 1024^2 (whole run of 15) 24 / 64.
+// per workgroup, 16 per thread) 22 / 45.  Planes, FP64: 128^2 3.9 / 12.1, 256^2 4.9 / 13.3,
+// 512^2 6.4 / 24.2, 1024^2 (whole run of 15) 24 / 64.
 // FP64 with 16 cells per thread (112^3, 128^3): 32.9 / 46.9, 37.5 / 51.4; half of it is what
 // goes past the L2 (the iterate, 33 MB an iteration, and the halo, 44 MB, at about 4.5 TB/s),
 // and it still spills 38 registers.  Planes above about 1000^2 do not fit; smaller grids are
