@@ -30,9 +30,14 @@ struct Tile {
     static constexpr int kCoarseX = TX / 2 + 1, kCoarse = kCoarseX * (TY / 2 + 1);
 };
 // EXP_true at 512^3: 64 x 8 605 us, 128 x 4 512 us (long rows: fewer lines split between
-// tiles), 256 x 2 568 us; the interpolation at 256^3: 64 x 8 86 us, 128 x 4 98 us.
+// tiles), 256 x 2 568 us.  The interpolation (EXP_finite at 256^3 as a whole): one node per
+// thread, 64 x 8, 89 us: lanes on Z1 planes of x waited for those between, and 184 registers
+// left one workgroup per CU; two nodes per thread, one plane of Z1 at a time, 71 us with 166
+// registers, 66 with 128.
 using MidTile = Tile<128, 4>;
-using CellTile = Tile<64, 8>;
+using CellTile = Tile<64, 16>;
+constexpr int kCellThreads = CellTile::kThreads / 2;    // two nodes each
+constexpr int kCellWaves = 4;                           // per SIMD: 128 registers
 
 // Midpoint extrapolation of the grid of N cells (even) from the fine solution H on it and the
 // coarse one C on every second node.  Nodes of the coarse grid: eq. (t1) (TRUE: (4 H - C) / 3)
@@ -129,98 +134,111 @@ __device__ __forceinline__ double lagrange(int pos, int node) {
 // fine cells.  A node at an odd position of an axis takes the cell's three Z1 planes of that
 // axis, at an even one the plane it lies on; terms are summed in the node order of the cell
 // (z slowest, x fastest).  (The weights are multiples of 1/512, so their products are exact.)
-template <int NX, int NY>
-__device__ __forceinline__ void interpolate(const double *const (&P)[3], int at, int px, int py,
-                                            double (&out)[4]) {
-    double v[3][NY][NX], wxy[NY][NX];
+// A thread takes the nodes 2t (on a Z1 plane of x) and 2t+1 (between) of a row, whose Z1 nodes
+// it reads once, for the four fine planes of a cell.
+template <int NY>
+__device__ __forceinline__ void interpolate(const double *const (&P)[3], int at, int second, int py,
+                                            double (&even)[4], double (&odd)[4]) {
+    const int px = second ? 3 : 1;
+    double wxy[NY][3], wy[NY];
 #pragma unroll
-    for (int y = 0; y < NY; y++)
+    for (int y = 0; y < NY; y++) {
+        wy[y] = NY == 1 ? 1.0 : lagrange(py, y);
 #pragma unroll
-        for (int x = 0; x < NX; x++) {
-            wxy[y][x] = (NX == 1 ? 1.0 : lagrange(px, x)) * (NY == 1 ? 1.0 : lagrange(py, y));
+        for (int x = 0; x < 3; x++) wxy[y][x] = lagrange(px, x) * wy[y];
+    }
 #pragma unroll
-            for (int z = 0; z < 3; z++) v[z][y][x] = P[z][at + y * CellTile::kCoarseX + x];
+    for (int c = 0; c < 4; c++) even[c] = odd[c] = 0.0;
+#pragma unroll
+    for (int z = 0; z < 3; z++) {
+        double v[NY][3], ve[NY];
+#pragma unroll
+        for (int y = 0; y < NY; y++) {
+#pragma unroll
+            for (int x = 0; x < 3; x++) v[y][x] = P[z][at + y * CellTile::kCoarseX + x];
+            ve[y] = second ? v[y][1] : v[y][0];
         }
 #pragma unroll
-    for (int c = 0; c < 4; c++) {
-        if (NX == 1 && NY == 1 && (c & 1) == 0) {
-            out[c] = v[c / 2][0][0];
-            continue;
-        }
-        double val = 0.0;
-#pragma unroll
-        for (int z = 0; z < 3; z++) {
+        for (int c = 0; c < 4; c++) {
             if ((c & 1) == 0 && z != c / 2) continue;
             const double wz = (c & 1) == 0 ? 1.0 : lagrange(c, z);
 #pragma unroll
-            for (int y = 0; y < NY; y++)
+            for (int y = 0; y < NY; y++) {
+                even[c] = NY == 1 && (c & 1) == 0 ? ve[y] : even[c] + (wy[y] * wz) * ve[y];
 #pragma unroll
-                for (int x = 0; x < NX; x++) val = val + (wxy[y][x] * wz) * v[z][y][x];
+                for (int x = 0; x < 3; x++) odd[c] = odd[c] + (wxy[y][x] * wz) * v[y][x];
+            }
         }
-        out[c] = val;
     }
 }
 
-__global__ void __launch_bounds__(CellTile::kThreads)
+__global__ void __launch_bounds__(kCellThreads, kCellWaves)
     k_interpolate(int N, int cells, const double *V, double *out) {
     constexpr int kTileX = CellTile::kX, kTileY = CellTile::kY, kCoarseX = CellTile::kCoarseX,
                   kCoarse = CellTile::kCoarse;
     __shared__ double sv[5][kCoarse];
-    const int tx = threadIdx.x, ty = threadIdx.y, tid = ty * kTileX + tx;
-    const int i = blockIdx.x * kTileX + tx, j = blockIdx.y * kTileY + ty;
+    // a wave takes two rows of 32 pairs whose positions in y are both on or both between Z1's
+    const int tid = threadIdx.x, wave = tid >> 6, t = tid & 31;
+    const int ty = 4 * (wave >> 1) + (wave & 1) + 2 * ((tid >> 5) & 1);
+    const int i = blockIdx.x * kTileX + 2 * t, j = blockIdx.y * kTileY + ty;
     const int N1 = N / 2, N0 = N / 4;
     const int c0 = blockIdx.z * cells, c1 = min(c0 + cells, N0);
     const i64 M = (i64)N + 1, M1 = (i64)N1 + 1, plane1 = M1 * M1;
-    const bool valid = i <= N && j <= N;
-    // staging: two planes of Z1 a step (threads 0 .. 2 kCoarse - 1)
-    const int half = tid >= kCoarse ? 1 : 0, node = tid - half * kCoarse;
-    const bool stages = tid < 2 * kCoarse;
-    const int I = min((int)blockIdx.x * (kTileX / 2) + node % kCoarseX, N1),
-              J = min((int)blockIdx.y * (kTileY / 2) + node / kCoarseX, N1);
-    const double *src = V + (i64)J * M1 + I;
-    // this node's first Z1 node in the tile, and its position in the cell
-    const int px = tx & 3, py = ty & 3;
-    const int at = ((px & 1) ? 2 * (tx >> 2) : tx >> 1) +
-                   ((py & 1) ? 2 * (ty >> 2) : ty >> 1) * kCoarseX;
+    const bool valid = i <= N && j <= N, pair = valid && i < N;
+    // staging: two planes of Z1 a step, in turns
+    constexpr int kLoads = (2 * kCoarse + kCellThreads - 1) / kCellThreads;
+    auto source = [&](int k, int plane) {
+        const int e = tid + k * kCellThreads, half = e >= kCoarse ? 1 : 0, node = e - half * kCoarse;
+        const int I = min((int)blockIdx.x * (kTileX / 2) + node % kCoarseX, N1),
+                  J = min((int)blockIdx.y * (kTileY / 2) + node / kCoarseX, N1);
+        return e < 2 * kCoarse ? V[min(plane + half, N1) * plane1 + (i64)J * M1 + I] : 0.0;
+    };
+    // the cell's first Z1 node in the tile, and the row's position in it
+    const int second = t & 1, py = ty & 3;
+    const int at = 2 * (t >> 1) + ((py & 1) ? 2 * (ty >> 2) : ty >> 1) * kCoarseX;
 
-    if (tid < kCoarse) sv[(2 * c0) % 5][tid] = src[2 * c0 * plane1];
-    double next = stages ? src[min(2 * c0 + 1 + half, N1) * plane1] : 0.0;
-    for (int c = c0; c < c1; c++) {
-        if (stages) sv[(2 * c + 1 + half) % 5][node] = next;
-        __syncthreads();
-        if (stages) next = src[min(2 * c + 3 + half, N1) * plane1];
-        const double *const P[3] = {sv[(2 * c) % 5], sv[(2 * c + 1) % 5], sv[(2 * c + 2) % 5]};
-        double o[4];
-        if (py & 1) {
-            if (px & 1) interpolate<3, 3>(P, at, px, py, o);
-            else interpolate<1, 3>(P, at, px, py, o);
-        } else {
-            if (px & 1) interpolate<3, 1>(P, at, px, py, o);
-            else interpolate<1, 1>(P, at, px, py, o);
-        }
-        if (valid) {
-            double *w = out + ((i64)(4 * c) * M + j) * M + i;
+    for (int e = tid; e < kCoarse; e += kCellThreads) {
+        const int I = min((int)blockIdx.x * (kTileX / 2) + e % kCoarseX, N1),
+                  J = min((int)blockIdx.y * (kTileY / 2) + e / kCoarseX, N1);
+        sv[(2 * c0) % 5][e] = V[2 * c0 * plane1 + (i64)J * M1 + I];
+    }
+    double next[kLoads];
 #pragma unroll
-            for (int k = 0; k < 4; k++) w[k * M * M] = o[k];
+    for (int k = 0; k < kLoads; k++) next[k] = source(k, 2 * c0 + 1);
+    for (int c = c0; c < c1; c++) {
+#pragma unroll
+        for (int k = 0; k < kLoads; k++) {
+            const int e = tid + k * kCellThreads, half = e >= kCoarse ? 1 : 0;
+            if (e < 2 * kCoarse) sv[(2 * c + 1 + half) % 5][e - half * kCoarse] = next[k];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kLoads; k++) next[k] = source(k, 2 * c + 3);
+        const double *const P[3] = {sv[(2 * c) % 5], sv[(2 * c + 1) % 5], sv[(2 * c + 2) % 5]};
+        double even[4], odd[4];
+        if (py & 1) interpolate<3>(P, at, second, py, even, odd);
+        else interpolate<1>(P, at, second, py, even, odd);
+        double *w = out + ((i64)(4 * c) * M + j) * M + i;
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            if (valid) w[k * M * M] = even[k];
+            if (pair) w[k * M * M + 1] = odd[k];
         }
     }
-    if (c1 == N0 && valid) {       // the last plane of nodes
+    if (c1 == N0) {       // the last plane of nodes
         const double *const P[3] = {sv[(2 * N0) % 5], sv[(2 * N0) % 5], sv[(2 * N0) % 5]};
-        double o[4];
-        if (py & 1) {
-            if (px & 1) interpolate<3, 3>(P, at, px, py, o);
-            else interpolate<1, 3>(P, at, px, py, o);
-        } else {
-            if (px & 1) interpolate<3, 1>(P, at, px, py, o);
-            else interpolate<1, 1>(P, at, px, py, o);
-        }
-        out[((i64)N * M + j) * M + i] = o[0];
+        double even[4], odd[4];
+        if (py & 1) interpolate<3>(P, at, second, py, even, odd);
+        else interpolate<1>(P, at, second, py, even, odd);
+        double *w = out + ((i64)N * M + j) * M + i;
+        if (valid) w[0] = even[0];
+        if (pair) w[1] = odd[0];
     }
 }
 
 // Steps per workgroup: long marches stage fewer shared planes, `groups` workgroups or more
-// hide the loads (EXP_true at 512^3: 2048 groups 573 us, 4096 550, 16384 512; the
-// interpolation holds 184 registers and gains nothing beyond 1024).
+// hide the loads (EXP_true at 512^3: 2048 groups 573 us, 4096 550, 16384 512; EXP_finite at
+// 256^3 / 384^3: 512 groups 64 / 280 us, 1024 66 / 252, 2048 69 / 238).
 int march_steps(int tiles, int steps, int groups) {
     const int want = std::max(1, groups / tiles);
     return std::max(std::min(steps, 2), (steps + want - 1) / want);
@@ -245,7 +263,7 @@ hipError_t exp_finite(int N, const double *u1, const double *u0, double *v_scrat
     const int tx = N / CellTile::kX + 1, ty = N / CellTile::kY + 1, N0 = N / 4;
     const int cells = march_steps(tx * ty, N0, 1024);
     hipLaunchKernelGGL(k_interpolate, dim3(tx, ty, (N0 + cells - 1) / cells),
-                       dim3(CellTile::kX, CellTile::kY), 0, st, N, cells, v_scratch, w);
+                       dim3(kCellThreads), 0, st, N, cells, v_scratch, w);
     return hipGetLastError();
 }
 
