@@ -772,6 +772,7 @@ int bicg_resident(const Level &L, double *x, BicgState &hs, bool *done) {
     run.slots = c.res_slots.p;
     run.epoch = c.res_epoch;
     run.one_xcd = plan.one_xcd;
+    run.look = plan.look;
     if (resident_run<T>(plan, run, g_stream) != hipSuccess) {
         (void)hipGetLastError();
         c.res_off = true;
@@ -1974,6 +1975,7 @@ struct BatchSolver {
             R.cells = (char *)res.cells.p + cell0;
             R.slots = (char *)res.slots.p + k * slot_bytes;
             R.epoch = res.epoch;
+            R.look = P.look;
             R.min_steps = (unsigned)std::max(1.0, kBatchWindow / P.us);
             R.max_steps = others ? (unsigned)std::max(1.0, kBatchTurn / P.us) : ~0u;
             R.stop = res.flags.as<unsigned>();

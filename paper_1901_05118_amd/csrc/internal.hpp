@@ -223,6 +223,7 @@ struct ResidentPlan {
     bool one_xcd = false;          // workgroups on one XCD, which exchange in its L2
     size_t lds = 0, exchange = 0;  // bytes of LDS; of exchanged cells
     double us = 0.0;               // modelled time of an iteration
+    int look = 0;                  // rest before the partials of rho' are looked for (256 cycles)
 };
 template <typename T>
 struct ResidentRun {
@@ -239,6 +240,7 @@ struct ResidentRun {
     void *slots;                   // exchanged partials: 6 planes of 16 bytes per workgroup (256)
     unsigned epoch;                // the run's exchanges are numbered from epoch + 1
     bool one_xcd;                  // ResidentPlan::one_xcd
+    int look;                      // ResidentPlan::look
     // a run of a batch (r and r* are also written when it is halted; x_work may be x)
     unsigned min_steps, max_steps; // iterations before it may be, and is, halted
     unsigned *stop;                // the launch's: epoch + 1 once a run has stopped

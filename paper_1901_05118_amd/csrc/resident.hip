@@ -26,7 +26,7 @@
 // Measured choices: exchanged cells in mailboxes, contiguous per reader, against cells in
 // grid order, each word proving itself: 64^3 10.6 -> 8.5 us, 96^3 22.3 -> 17.5 us (half the
 // bytes and whole lines: what the CUs can load past the L2 bounds the exchange); q* formed
-// while sigma's partials travel; partials first looked for kFirstLook after they are sent
+// while sigma's partials travel; partials first looked for some time after they are sent
 // (at once: 32^3 6.1 -> 5.3 us, a look that comes too early costs another); the iterate in
 // registers, not in memory (96^3 32 -> 26 us).
 //
@@ -56,8 +56,6 @@ typedef unsigned long long u64;
 
 namespace {
 
-constexpr int kFirstLook = 24;              // s_sleep units (64 cycles)
-constexpr int kFirstLookL2 = 4;             // (on one XCD)
 constexpr u64 kWaitTicks = 200000000ull;    // 2 s of the 100 MHz constant clock
 
 // Exchanged memory is accessed 16 bytes at a time, at agent scope (sc1: past the L2 that the
@@ -465,6 +463,11 @@ void for_plans(int n, int dim, bool fp64, bool batch, Use use) {
                         p.one_xcd = true;
                         p.us -= 0.514;
                     }
+                    // The partials of rho' come when the slowest workgroup has sent its own, the
+                    // later the longer an iteration is; looks before that delay what they wait
+                    // for.  (256 cycles: 28^3 best 5, 48^3 8, 64^3 10-12, 96^3 16; looking at
+                    // once 1 us slower throughout, at 6 everywhere 8% at 48^3, 4% at 64^3.)
+                    p.look = p.one_xcd ? 1 : (int)std::min(16.0, std::max(5.0, 1.2 * p.us));
                     use(p);
                 }
 }
@@ -475,8 +478,8 @@ void for_plans(int n, int dim, bool fp64, bool batch, Use use) {
 // (us), fitted to 800 partitions of 3D grids of 12 to 96 cells (FP64; what it picks takes 3%
 // longer than the best of each grid, 9% at most): work per wave and per thread, exchanges that
 // grow with the number of workgroups, cells exchanged.  Measured per iteration against the
-// launch-per-sweep form: 16^3 4.7 / 17.9, 32^3 5.2 / 18.3, 48^3 7.1 / 21.3, 64^3 9.7 / 26.1,
-// 96^3 16.5 / 45.0 us.  FP32 vectors: 96^3 13.4 / 37.3, 112^3 20.1 / 48.9, 128^3 (8192 cells
+// launch-per-sweep form: 16^3 4.7 / 17.9, 32^3 5.2 / 18.3, 48^3 6.8 / 21.3, 64^3 9.4 / 26.1,
+// 96^3 15.8 / 45.0 us.  FP32 vectors: 96^3 13.4 / 37.3, 112^3 20.1 / 48.9, 128^3 (8192 cells
 // per workgroup, 16 per thread) 22 / 45.  Planes, FP64: 128^2 3.9 / 12.1, 256^2 4.9 / 13.3,
 // 512^2 6.4 / 24.2, 1024^2 (whole run of 15) 24 / 64.
 // FP64 with 16 cells per thread (112^3, 128^3): 32.9 / 46.9, 37.5 / 51.4; half of it is what

@@ -457,8 +457,7 @@
         }
         if (MULTI) {
             // A load takes about 1800 cycles (past the L2); asked too early it is asked twice.
-            if (l2) __builtin_amdgcn_s_sleep(kFirstLookL2);
-            else if (!kLean) __builtin_amdgcn_s_sleep(kFirstLook);
+            for (int k = a.look; k > 0; k--) __builtin_amdgcn_s_sleep(4);
             if (64 * (wave >> 1) < W) {     // even waves: rho', odd waves: r.r
                 const int w = (wave >> 1) * 64 + lane;
                 const Pair v = gather_pairs(xs, w < W ? 16u * (unsigned)w : kNoPlace,
