@@ -13,6 +13,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -2292,13 +2293,17 @@ int static_scratch(double **out) {
 
 // The intermediate grid of excmg_exp_finite, kept from call to call (every call waits for its
 // work): an allocation and a free took 80 of the call's 381 us at 256^3.
-// Only up to kExpKeep bytes, on the device of the last call; given back by excmg_finalize.
+// Only up to kExpKeep bytes, on the device of the last call, and for one call at a time (one
+// that overlaps with it allocates its own); given back by excmg_finalize.
 constexpr size_t kExpKeep = (size_t)64 << 20;
 DBuf g_exp_scratch;
 int g_exp_device = -1;
 
-int exp_scratch(size_t bytes, DBuf &once, DBuf **out) {
-    if (bytes > kExpKeep) {
+std::mutex g_exp_mutex;
+
+// `turn` is held until the call's work is done.
+int exp_scratch(size_t bytes, std::unique_lock<std::mutex> &turn, DBuf &once, DBuf **out) {
+    if (bytes > kExpKeep || !turn.try_lock()) {
         *out = &once;
         return once.ensure(bytes);
     }
@@ -2518,16 +2523,18 @@ int excmg_exp_finite(int n, const double *u1, const double *u0, double *w) {
     CKR(a1.in());
     CKR(a0.in());
     CKR(aw.out());
+    std::unique_lock<std::mutex> turn(g_exp_mutex, std::defer_lock);
     DBuf once;
     DBuf *v = nullptr;
-    CKR(exp_scratch(m1 * m1 * m1 * 8, once, &v));
+    CKR(exp_scratch(m1 * m1 * m1 * 8, turn, once, &v));
     hipError_t e = exp_finite(n, a1.p<double>(), a0.p<double>(), v->as<double>(), aw.p<double>(),
                               g_stream);
-    if (e == hipSuccess && v == &once) e = hipStreamSynchronize(g_stream);
+    const int rc = e == hipSuccess ? aw.back() : EXCMG_OK;
+    const hipError_t done = hipStreamSynchronize(g_stream);
     once.release();
     CKH(e);
-    CKR(aw.back());
-    CKH(hipStreamSynchronize(g_stream));
+    CKR(rc);
+    CKH(done);
     return EXCMG_OK;
 }
 
@@ -3066,7 +3073,10 @@ const char *excmg_last_error(void) { return g_err; }
 
 void excmg_finalize(void) {
     (void)hipStreamSynchronize(g_stream);
-    g_exp_scratch.release();
+    {
+        std::lock_guard<std::mutex> turn(g_exp_mutex);
+        g_exp_scratch.release();
+    }
     g_ctx.release();
 }
 
