@@ -336,7 +336,7 @@ typedef struct excmg_problem {
 
 /* Algorithm 1 for nprob independent problems (1..256) of possibly different grids, levels
  * and boundary kinds, advanced together.  opts.batch_mode 0: levels whose Bi-CG vectors fit on
- * the chip (FP64 up to about 100^3, FP32 up to 128^3) run resident, several systems in one
+ * the chip (up to 128^3) run resident, several systems in one
  * cooperative launch; one Bi-CG iteration of all other running systems is four phase launches.
  * batch_mode 1: one launch of a persistent work-queue kernel per iteration of all systems.
  * Steps are replayed in windows from captured hipGraphs.  Each problem follows its own cascade,

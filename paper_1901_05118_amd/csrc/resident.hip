@@ -389,7 +389,7 @@ constexpr int max_threads(int C, bool fp64, int dim) {
 }
 // (a run of a batch: FP32 with at least 4 cells per thread)
 constexpr int max_batch_threads(int C, bool fp64) {
-    return C == 16 && fp64 ? 0 : C <= 2 && !fp64 ? 0 : 512;
+    return C <= 2 && !fp64 ? 0 : 512;
 }
 constexpr int kXcdGroups = 32;              // CUs of an XCD
 constexpr size_t kMaxLds = 158 * 1024;     // of 160 KB per workgroup; the rest is static
@@ -560,7 +560,8 @@ __device__ __forceinline__ void batch_run(const EXCMG_CONSTANT ResidentRun<T> &a
 // The waves that a run's partition has no work for end here (a barrier waits for the
 // workgroup's remaining waves only).  24 problems of 32^3 to 128^3 in mixed precision: 775 ms
 // by steps of four launches (20 us a step at the least), 312 ms resident, of which 223 in 91
-// launches; one after the other with launches of their own they take 376 ms.
+// launches; one after the other with launches of their own they take 376 ms.  In FP64 830 by
+// steps, 358 resident (480 with the 128^3 systems by steps).
 __global__ void __launch_bounds__(512) k_resident_batch(const ResidentBatchRun *table, int count) {
     extern __shared__ char lds_raw[];
     __shared__ ResidentShared sh;
@@ -585,6 +586,8 @@ __global__ void __launch_bounds__(512) k_resident_batch(const ResidentBatchRun *
         EXCMG_BATCH_RUN(double, 4, 36)
         EXCMG_BATCH_RUN(double, 8, 20)
         EXCMG_BATCH_RUN(double, 8, 36)
+        EXCMG_BATCH_RUN(double, 16, 20)
+        EXCMG_BATCH_RUN(double, 16, 36)
         EXCMG_BATCH_RUN(float, 4, 20)
         EXCMG_BATCH_RUN(float, 4, 36)
         EXCMG_BATCH_RUN(float, 8, 20)

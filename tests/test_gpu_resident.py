@@ -113,11 +113,11 @@ def test_mixed_plane_equals_sweeps(ex, N, levels, bc):
 
 @pytest.mark.parametrize("case", ["fp64", "mixed", "mixed small", "capped"])
 def test_batch_runs_equal_steps(ex, case):
-    """Runs of a batch in shared launches (more of them than there are CUs for; one grid that
-    is advanced by steps beside them) against the persistent steps, which take all systems."""
+    """Runs of a batch in shared launches (more of them than there are CUs for; 160^3 advances by
+    steps beside them) against the persistent steps, which take all systems."""
     print(f"resident batch {case}", flush=True)
     sizes = [(16, 3), (24, 4), (40, 4), (48, 5), (64, 5), (64, 5), (80, 5), (96, 6), (28, 3), (32, 4)]
-    sizes += {"fp64": [(112, 5)], "mixed": [(96, 5), (128, 6)]}.get(case, [])
+    sizes += {"fp64": [(112, 5)], "mixed": [(96, 5), (128, 6)], "capped": [(160, 6)]}.get(case, [])
     probs, fields = [], []
     for j, (N, nl) in enumerate(sizes):
         arr = make_arrays(config_problem(2), N, 1 + j % 2)
