@@ -314,6 +314,25 @@ int excmg_profile_sweep(int which, int precision, int reps, double *ms_per_launc
 int excmg_set_timing(int on);
 int excmg_get_timing(int level, int sweep, double *ms_total, long long *launches);
 
+/* Control of the resident launches (whole Bi-CG runs in one cooperative launch), for tests of
+ * what follows when one is refused by the device or when its workgroups wait for each other in
+ * vain (2 s): results are the same, or as good, by the launch-per-sweep form.  Launches are
+ * counted from the last reset, which also takes back the rest.
+ *   EXCMG_RESIDENT_REFUSE   launch `value` and later ones are refused (-1: none)
+ *   EXCMG_RESIDENT_EXPIRE   waits of launch `value` end after EXCMG_RESIDENT_WAIT (-1: none)
+ *   EXCMG_RESIDENT_PROBLEM  ... for the run of problem `value` of a batch alone (-1: all)
+ *   EXCMG_RESIDENT_WAIT     ticks of 10 ns (0: one look)
+ *   EXCMG_RESIDENT_NUMBER   number that the exchanges of a new context or batch start from
+ * excmg_resident_counts: launches since then, and those refused or given up. */
+#define EXCMG_RESIDENT_RESET 0
+#define EXCMG_RESIDENT_REFUSE 1
+#define EXCMG_RESIDENT_EXPIRE 2
+#define EXCMG_RESIDENT_PROBLEM 3
+#define EXCMG_RESIDENT_WAIT 4
+#define EXCMG_RESIDENT_NUMBER 5
+int excmg_resident_control(int what, long long value);
+int excmg_resident_counts(long long *launches, long long *gave_up);
+
 /* Launch shape of the z-marched stencil kernels on grids of n cells: tiles of 64 x ty
  * columns marching through chunks of zc planes.  kind 0: the one-array kernels (operator,
  * residual; ty = 4, 8 or 16); kind 1 / 2: Bi-CG sweep A on FP64 / FP32 vectors (two arrays;

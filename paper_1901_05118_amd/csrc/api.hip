@@ -225,6 +225,32 @@ struct Ctx {
 
 Ctx g_ctx;
 
+// Resident launches since the control's last reset, those of them that gave up or were refused,
+// and what the control asks of later ones (see excmg_resident_control).
+struct ResidentControl {
+    long long launches = 0, gave_up = 0;
+    long long refuse = -1, expire = -1, problem = -1, wait = 0, number = 0;
+};
+ResidentControl g_res;
+
+// Makes one resident launch (`launch`), unless the control refuses it.
+template <class Launch>
+bool resident_launch(Launch launch) {
+    const long long k = g_res.launches++;
+    if (g_res.refuse < 0 || k < g_res.refuse) {
+        if (launch() == hipSuccess) return true;
+        (void)hipGetLastError();
+    }
+    g_res.gave_up++;
+    return false;
+}
+
+// Longest wait of the next resident launch's run of problem j (0: a run of its own).
+unsigned long long resident_wait(long long j) {
+    const bool expires = g_res.launches == g_res.expire && (g_res.problem < 0 || g_res.problem == j);
+    return expires ? (unsigned long long)g_res.wait : kResidentWait;
+}
+
 // Optional per-launch timing of the two Bi-CG sweeps (device events on the library stream),
 // accumulated per level: [level][0] sweep A, [level][1] sweep B.
 bool g_timing = false;
@@ -748,7 +774,7 @@ int bicg_resident(const Level &L, double *x, BicgState &hs, bool *done) {
         }
         CKH(hipMemsetAsync(c.res_cells.p, 0, c.res_cells.bytes, g_stream));
         CKH(hipMemsetAsync(c.res_slots.p, 0, c.res_slots.bytes, g_stream));
-        c.res_epoch = 0;
+        c.res_epoch = wrap ? 0 : (unsigned)g_res.number;
     }
     ResidentRun<T> run{};
     run.n = L.n;
@@ -774,8 +800,8 @@ int bicg_resident(const Level &L, double *x, BicgState &hs, bool *done) {
     run.epoch = c.res_epoch;
     run.one_xcd = plan.one_xcd;
     run.look = plan.look;
-    if (resident_run<T>(plan, run, g_stream) != hipSuccess) {
-        (void)hipGetLastError();
+    run.wait = resident_wait(0);
+    if (!resident_launch([&] { return resident_run<T>(plan, run, g_stream); })) {
         c.res_off = true;
         return EXCMG_OK;
     }
@@ -787,6 +813,7 @@ int bicg_resident(const Level &L, double *x, BicgState &hs, bool *done) {
         // here on.  x, r and r* are as they were; a resumed run's directions may not be, and
         // it ends as a breakdown does, which starts a fresh run
         c.res_off = true;
+        g_res.gave_up++;
         if (hs.iter > 0) {
             hs.status = kBreakdown;
             *done = true;
@@ -1943,7 +1970,7 @@ struct BatchSolver {
             }
             CKH(hipMemsetAsync(res.slots.p, 0, res.slots.bytes, st));
             CKH(hipMemsetAsync(res.flags.p, 0, res.flags.bytes, st));
-            res.epoch = 0;
+            res.epoch = wrap ? 0 : (unsigned)g_res.number;
         }
         int blocks = 0;
         size_t cell0 = 0;
@@ -1977,6 +2004,7 @@ struct BatchSolver {
             R.slots = (char *)res.slots.p + k * slot_bytes;
             R.epoch = res.epoch;
             R.look = P.look;
+            R.wait = resident_wait(run[k].j);
             R.min_steps = (unsigned)std::max(1.0, kBatchWindow / P.us);
             R.max_steps = others ? (unsigned)std::max(1.0, kBatchTurn / P.us) : ~0u;
             R.stop = res.flags.as<unsigned>();
@@ -1987,11 +2015,10 @@ struct BatchSolver {
         }
         CKH(hipMemcpyAsync(res.table.p, res.h_table, run.size() * sizeof(ResidentBatchRun),
                            hipMemcpyHostToDevice, st));
-        if (resident_batch(res.table.as<ResidentBatchRun>(), (int)run.size(), blocks, lds, st) != hipSuccess) {
-            (void)hipGetLastError();
-            return resident_stop();
-        }
-        return EXCMG_OK;
+        const bool made = resident_launch([&] {
+            return resident_batch(res.table.as<ResidentBatchRun>(), (int)run.size(), blocks, lds, st);
+        });
+        return made ? EXCMG_OK : resident_stop();
     }
 
     // From here on the steps take every system.
@@ -2022,7 +2049,9 @@ struct BatchSolver {
             }
         }
         res.epoch += used + 2;
-        return late ? resident_stop() : EXCMG_OK;
+        if (!late) return EXCMG_OK;
+        g_res.gave_up++;
+        return resident_stop();
     }
 
     int run() {
@@ -3066,6 +3095,32 @@ int excmg_get_shape(int n, int kind, int *ty, int *zc) {
     Geom g = choose_shape(n, 1, kind);
     if (ty) *ty = g.ty;
     if (zc) *zc = g.zc;
+    return EXCMG_OK;
+}
+
+int excmg_resident_control(int what, long long value) {
+    g_err[0] = 0;
+    switch (what) {
+        case EXCMG_RESIDENT_RESET: g_res = ResidentControl{}; return EXCMG_OK;
+        case EXCMG_RESIDENT_REFUSE: g_res.refuse = value; return EXCMG_OK;
+        case EXCMG_RESIDENT_EXPIRE: g_res.expire = value; return EXCMG_OK;
+        case EXCMG_RESIDENT_PROBLEM: g_res.problem = value; return EXCMG_OK;
+        case EXCMG_RESIDENT_WAIT:
+            if (value < 0 || value > (long long)kResidentWait) return fail(EXCMG_EINVAL, "wait out of range");
+            g_res.wait = value;
+            return EXCMG_OK;
+        case EXCMG_RESIDENT_NUMBER:
+            if (value < 0 || value > 0xffffffffll) return fail(EXCMG_EINVAL, "number out of range");
+            g_res.number = value;
+            return EXCMG_OK;
+        default: return fail(EXCMG_EINVAL, "no such control");
+    }
+}
+
+int excmg_resident_counts(long long *launches, long long *gave_up) {
+    g_err[0] = 0;
+    if (launches) *launches = g_res.launches;
+    if (gave_up) *gave_up = g_res.gave_up;
     return EXCMG_OK;
 }
 

@@ -241,6 +241,7 @@ struct ResidentRun {
     unsigned epoch;                // the run's exchanges are numbered from epoch + 1
     bool one_xcd;                  // ResidentPlan::one_xcd
     int look;                      // ResidentPlan::look
+    unsigned long long wait;       // longest wait for other workgroups (ticks of 10 ns)
     // a run of a batch (r and r* are also written when it is halted; x_work may be x)
     unsigned min_steps, max_steps; // iterations before it may be, and is, halted
     unsigned *stop;                // the launch's: epoch + 1 once a run has stopped
@@ -249,6 +250,7 @@ struct ResidentRun {
 bool resident_plan(int n, int dim, bool fp64, ResidentPlan &plan);
 template <typename T>
 hipError_t resident_run(const ResidentPlan &plan, const ResidentRun<T> &run, hipStream_t st);
+constexpr unsigned long long kResidentWait = 200000000ull;    // 2 s
 
 // Several 3D runs in one cooperative launch, each on its share of the workgroups.
 constexpr int kBatchShares = 6;

@@ -42,7 +42,7 @@
 // between launch shapes.
 //
 // The workgroups wait for each other, so they are launched cooperatively (one per CU, all
-// resident) and every wait is bounded: past kWaitTicks the launch gives up (err set, the
+// resident) and every wait is bounded: past the run's `wait` the launch gives up (err set, the
 // caller's vectors untouched) and the host runs the launch-per-sweep form instead.
 #include <algorithm>
 
@@ -55,8 +55,6 @@ namespace excmg {
 typedef unsigned long long u64;
 
 namespace {
-
-constexpr u64 kWaitTicks = 200000000ull;    // 2 s of the 100 MHz constant clock
 
 // Exchanged memory is accessed 16 bytes at a time, at agent scope (sc1: past the L2 that the
 // XCDs do not share): two 8-byte words of {4 bytes of data, exchange number}, each proving
@@ -197,11 +195,11 @@ __device__ __forceinline__ void wave_merge_n(Pair (&v)[NV]) {
 
 // The pairs of one value of up to 64 workgroups (`place`: this lane's in the exchange memory,
 // kNoPlace: none; its sum and its compensation in two planes), merged over the wave.  Sets
-// *bad when the wait runs out.
+// *bad when it has waited for `wait` ticks of the constant clock (0: for one look).
 constexpr int kMaxGroups = 256;
 constexpr unsigned kSlotPlane = kMaxGroups * 16;
 __device__ __forceinline__ Pair gather_pairs(__amdgpu_buffer_rsrc_t slots, unsigned place,
-                                             unsigned plane, unsigned ep, int *bad) {
+                                             unsigned plane, unsigned ep, u64 wait, int *bad) {
     u32x4 s, c;
     const u64 t0 = wall_clock64();
     bool late = false;
@@ -210,7 +208,7 @@ __device__ __forceinline__ Pair gather_pairs(__amdgpu_buffer_rsrc_t slots, unsig
         s = get(slots, place, plane);
         c = get(slots, place, plane + kSlotPlane);
         if (__all((is_new(s, ep) && is_new(c, ep)) || place == kNoPlace)) break;
-        late = wall_clock64() - t0 > kWaitTicks;
+        late = wall_clock64() - t0 >= wait;
         if (late) break;
     }
     if (late) *bad = 1;
@@ -221,13 +219,14 @@ __device__ __forceinline__ Pair gather_pairs(__amdgpu_buffer_rsrc_t slots, unsig
 
 // Whether all of up to 64 workgroups sent this value.
 __device__ __forceinline__ bool gather_same(__amdgpu_buffer_rsrc_t slots, unsigned place,
-                                            unsigned plane, unsigned ep, unsigned value, int *bad) {
+                                            unsigned plane, unsigned ep, unsigned value, u64 wait,
+                                            int *bad) {
     const u64 t0 = wall_clock64();
     for (;;) {
         asm volatile("" ::: "memory");
         const u32x4 s = get(slots, place, plane);
         if (__all(is_new(s, ep) || place == kNoPlace)) return __all(s[0] == value || place == kNoPlace);
-        if (wall_clock64() - t0 > kWaitTicks) {
+        if (wall_clock64() - t0 >= wait) {
             *bad = 1;
             return false;
         }

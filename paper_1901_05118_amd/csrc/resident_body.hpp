@@ -182,7 +182,7 @@
             if (tid < 64) {
                 if (tid == 0) put<kAgent>(xs, 16u * (unsigned)blk, 2 * kSlotPlane, xcd, 0, ep);
                 const bool same = gather_same(xs, tid < W ? 16u * (unsigned)tid : kNoPlace,
-                                              2 * kSlotPlane, ep, xcd, &bad);
+                                              2 * kSlotPlane, ep, xcd, a.wait, &bad);
                 if (tid == 0) all_a[0].s = same ? 1.0 : 0.0;
             }
             __syncthreads();
@@ -347,7 +347,8 @@
         // ---- sigma and alpha
         if (MULTI) {
             if (64 * wave < W) {
-                const Pair v = gather_pairs(xs, tid < W ? 16u * (unsigned)tid : kNoPlace, 0, ep, &bad);
+                const Pair v = gather_pairs(xs, tid < W ? 16u * (unsigned)tid : kNoPlace, 0, ep, a.wait,
+                                            &bad);
                 if (lane == 0) all_a[wave] = v;
             }
             __syncthreads();
@@ -461,7 +462,7 @@
             if (64 * (wave >> 1) < W) {     // even waves: rho', odd waves: r.r
                 const int w = (wave >> 1) * 64 + lane;
                 const Pair v = gather_pairs(xs, w < W ? 16u * (unsigned)w : kNoPlace,
-                                            (2 + 2 * (wave & 1)) * kSlotPlane, ep, &bad);
+                                            (2 + 2 * (wave & 1)) * kSlotPlane, ep, a.wait, &bad);
                 if (lane == 0) all_b[wave] = v;
             }
             __syncthreads();

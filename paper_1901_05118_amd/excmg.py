@@ -19,7 +19,7 @@ __all__ = [
     "lib_path", "load", "set_stream", "setup", "apply_stencil", "apply_operator", "rhs", "dsolve", "bicg",
     "level_solve", "exp_finite", "exp_finite_noalloc", "exp_true", "solve", "solve_ex", "profile_sweep",
     "set_shape", "get_shape", "set_timing", "get_timing", "autotune", "solve_batch",
-    "autotune_batch", "get_batch_shape",
+    "autotune_batch", "get_batch_shape", "resident_control", "resident_counts",
     "get_level_solution", "setup_2d", "solve_ex_2d", "exp_finite_2d", "exp_true_2d",
     "Problem",
     "last_error", "finalize",
@@ -124,6 +124,8 @@ def load():
         "excmg_set_timing": (c_int, [c_int]),
         "excmg_get_timing": (c_int, [c_int, c_int, ctypes.POINTER(c_dbl),
                                      ctypes.POINTER(ctypes.c_longlong)]),
+        "excmg_resident_control": (c_int, [c_int, ctypes.c_longlong]),
+        "excmg_resident_counts": (c_int, [ctypes.POINTER(ctypes.c_longlong)] * 2),
         "excmg_set_shape": (c_int, [c_int, c_int, c_int, c_int]),
         "excmg_get_shape": (c_int, [c_int, c_int, ip, ip]),
         "excmg_last_error": (ctypes.c_char_p, []),
@@ -403,6 +405,26 @@ def get_timing(level: int, sweep: int):
     _check("excmg_get_timing", load().excmg_get_timing(level, sweep, ctypes.byref(ms),
                                                        ctypes.byref(n)))
     return ms.value, n.value
+
+
+RESIDENT_CONTROLS = {"refuse": 1, "expire": 2, "problem": 3, "wait": 4, "number": 5}
+
+
+def resident_control(**controls: int):
+    """Reset the control of the resident launches and their counts, then set the given ones:
+    refuse, expire, problem, wait, number (see excmg_resident_control)."""
+    fn = load().excmg_resident_control
+    _check("excmg_resident_control", fn(0, 0))
+    for name, value in controls.items():
+        _check("excmg_resident_control", fn(RESIDENT_CONTROLS[name], value))
+
+
+def resident_counts():
+    """(resident launches, those refused or given up) since the last resident_control()."""
+    made, gave_up = ctypes.c_longlong(0), ctypes.c_longlong(0)
+    _check("excmg_resident_counts", load().excmg_resident_counts(ctypes.byref(made),
+                                                                 ctypes.byref(gave_up)))
+    return made.value, gave_up.value
 
 
 def set_shape(n: int, kind: int, ty: int, zc: int):
