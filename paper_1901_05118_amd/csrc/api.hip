@@ -793,14 +793,16 @@ int bicg_resident(const Level &L, double *x, BicgState &hs, bool *done) {
     run.x = x;
     run.x_work = c.q.as<double>();
     run.state = c.state.as<BicgState>();
-    run.part = c.part_b.as<Pair>();
-    run.part_count = b_partials<double, T>(L);
     run.cells = c.res_cells.p;
     run.slots = c.res_slots.p;
     run.epoch = c.res_epoch;
     run.one_xcd = plan.one_xcd;
     run.look = plan.look;
     run.wait = resident_wait(0);
+    // a resumed run: rho and r.r of the replaced residual, and whether it stops there (decided
+    // ahead of the launch, whose workgroups could not agree on it without an exchange; the
+    // sweeps, if they take over, repeat it with the same result)
+    if (hs.iter > 0) CKR(close_window<T>(L, hs.iter, g_stream));
     if (!resident_launch([&] { return resident_run<T>(plan, run, g_stream); })) {
         c.res_off = true;
         return EXCMG_OK;
@@ -826,7 +828,7 @@ int bicg_resident(const Level &L, double *x, BicgState &hs, bool *done) {
         return EXCMG_OK;
     }
     c.res_epoch += (unsigned)(now.iter - iter0) + 3;
-    CKH((copy_convert<double, double>(L.nu, run.x_work, x, g_stream)));
+    if (now.iter > iter0) CKH((copy_convert<double, double>(L.nu, run.x_work, x, g_stream)));
     hs = now;
     *done = true;
     return EXCMG_OK;

@@ -233,9 +233,7 @@ struct ResidentRun {
     T *p[2], *ps[2];               // directions: read at a resumption, written at the end
     const double *x;               // iterate at the start
     double *x_work;                // iterate of the run (the caller's is left alone)
-    BicgState *state;              // as bicg_start or state_resume left it
-    const Pair *part;              // resumption: partials of r*.r and r.r
-    int part_count;
+    BicgState *state;              // as bicg_start left it, or (resumption) step_check or batch_resume
     void *cells;                   // exchanged cells (ResidentPlan::exchange bytes)
     void *slots;                   // exchanged partials: 6 planes of 16 bytes per workgroup (256)
     unsigned epoch;                // the run's exchanges are numbered from epoch + 1

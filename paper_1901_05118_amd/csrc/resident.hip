@@ -413,8 +413,8 @@ bool try_plan(int n, int dim, bool fp64, bool batch, int nbx, int nby, int nbz, 
     if (!one && (std::min(p.bx, p.bz) < 2 || (dim == 3 && p.by < 2))) return false;
     const int groups = (p.bz + C - 1) / C;
     const long long columns = (long long)p.bx * p.by * groups;
-    // at least the four waves of merge_fixed, and two waves per 64 workgroups to gather the
-    // partials of rho' and r.r
+    // at least a wave per SIMD (the model is fitted to no fewer), and two waves per 64 workgroups
+    // to gather the partials of rho' and r.r
     const long long waves = std::max({4LL, (columns + 63) / 64, (p.blocks + 63) / 64 * 2LL});
     if (64 * waves > (batch ? max_batch_threads(C, fp64) : max_threads(C, fp64, dim))) return false;
     if (batch && one) return false;

@@ -20,7 +20,9 @@
     const int PS = DIM == 3 ? BX * (by + 4) : BX, LE = PS * (groups * C + 4);
     BicgState *S = a.state;
     int status = S->status, iter = S->iter;
-    if (status != kRunning) {                  // uniform
+    // Uniform: a run that starts makes at least one exchange, so the state is written (by the
+    // first workgroup, at the end) only when every wave of the run has read it.
+    if (status != kRunning) {
         if (BATCH && blk == 0 && tid == 0)
             __hip_atomic_store(a.stop, a.epoch + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return;
@@ -116,21 +118,8 @@
     double rho = S->rho, rr = S->rr, beta = 0.0, alpha = S->alpha, sigma = S->sigma;
     double rho_old = rho;
     const bool first = (iter == 0);
+    if (!first) beta = S->beta;
     __syncthreads();
-    if (BATCH && !first) {
-        beta = S->beta;
-    } else if (!first) {
-        // rho of the replaced residual and the checks of the loop (see link_step)
-        rho_old = S->rho_slot[(iter & 1) ^ 1];
-        Pair v[2];
-        merge_fixed<2>(a.part, a.part_count, v, red);
-        rho = pair_value(v[0]);
-        rr = pair_value(v[1]);
-        if (rr <= thr) status = kConverged;
-        else if (iter >= maxit) status = kNoConv;
-        else if (rho == 0.0 || !isfinite(rho)) status = kBreakdown;
-        beta = rho / rho_old;
-    }
 
     // In the first iteration of a run p = r and p* = r*: the old directions are zeros and
     // beta is 0.

@@ -89,6 +89,25 @@ def test_refused_launches_of_fresh_and_resumed_runs(ex):
         np.testing.assert_array_equal(v, u)
 
 
+def test_resumed_run_with_nothing_to_do(ex):
+    """inner_tol 2: every replaced residual is below its threshold at once, so a resumed run stops
+    before its first iteration and leaves the iterate alone."""
+    N, levels, bc = 40, 4, 1
+    arr = make_arrays(config_problem(2), N, bc)
+    f, g1, g2 = dev(arr.f), dev(arr.g1), dev(arr.g2)
+    got = []
+    for control in ({}, dict(refuse=0)):
+        ex.finalize()
+        ex.resident_control(**control)
+        u = torch.empty_like(f)
+        rc, st = ex.solve_ex(N, levels, bc, f, g1, g2, 1e-7, u, precision=ex.MIXED,
+                             fp32_min_unknowns=1, inner_tol=2.0, max_outer=8)
+        assert rc == ex.ENOCONV
+        got.append(([(s["iterations"], s["runs"]) for s in st.levels()], u.cpu().numpy()))
+    assert got[0][0] == got[1][0]
+    np.testing.assert_array_equal(got[0][1], got[1][1])
+
+
 def test_exchange_numbers_wrap(ex):
     N, levels, bc = 40, 4, 1
     rng = np.random.default_rng(7)
