@@ -229,7 +229,7 @@ Ctx g_ctx;
 // and what the control asks of later ones (see excmg_resident_control).
 struct ResidentControl {
     long long launches = 0, gave_up = 0;
-    long long refuse = -1, expire = -1, problem = -1, wait = 0, number = 0;
+    long long refuse = -1, expire = -1, problem = -1, wait = 0, number = 0, turn = 0;
 };
 ResidentControl g_res;
 
@@ -705,11 +705,14 @@ int launch_iteration(const Level &L, TX *x, long long j, int ev, hipStream_t st,
 // With a deferred update pending the check only publishes its decision (poll_status): the
 // next sweep A stops the run after applying the update.
 template <typename T>
-int close_window(const Level &L, long long j_next, hipStream_t st, int defer = 0) {
+StepLink step_link(const Level &L, long long j_next, int defer = 0) {
     Ctx &c = g_ctx;
-    const StepLink l{c.state.as<BicgState>(), c.part_b.as<Pair>(), b_partials<double, T>(L), g_cg ? 1 : 2,
-                     (int)(j_next & 1), defer ? 1 : 0};
-    CKH(step_check(l, st));
+    return StepLink{c.state.as<BicgState>(), c.part_b.as<Pair>(), b_partials<double, T>(L), g_cg ? 1 : 2,
+                    (int)(j_next & 1), defer ? 1 : 0};
+}
+template <typename T>
+int close_window(const Level &L, long long j_next, hipStream_t st, int defer = 0) {
+    CKH(step_check(step_link<T>(L, j_next, defer), st));
     return EXCMG_OK;
 }
 
@@ -750,10 +753,15 @@ int window_graph(const Level &L, TX *x, int K, hipGraphExec_t *out, int defer = 
     return EXCMG_OK;
 }
 
-// The whole run in one resident launch, on grids and planes whose vectors fit on the chip (plain
-// Algorithm 2, contiguous rows, no explicit choice of the sweeps' form and no timing of
-// them).  *done = false: not taken (or given up, with nothing changed), and the
-// launch-per-sweep form runs.
+// A run in resident launches, on grids and planes whose vectors fit on the chip (Algorithm 2
+// with M = I and no dual iterate, contiguous rows, no explicit choice of the sweeps' form and no
+// timing of them).  A launch holds the chip, so it is halted after about kResidentTurn and
+// launched again, and other streams' work gets in between (a launch more costs 0.1 ms: with 10 ms
+// a turn the 37 ms of a 64^3 level became 1% slower, with 20 ms it is within the noise).
+// A launch leaves its inputs alone: when one is refused, or gives up, the run is where the one
+// before ended (*done = false), and the launch-per-sweep form goes on from there, from here on.
+constexpr double kResidentTurn = 20000.0;   // us
+
 template <typename T>
 int bicg_resident(const Level &L, double *x, BicgState &hs, bool *done) {
     Ctx &c = g_ctx;
@@ -764,18 +772,8 @@ int bicg_resident(const Level &L, double *x, BicgState &hs, bool *done) {
     const ResidentPlan &plan = c.resident(L, sizeof(T) == 8);
     if (plan.blocks == 0) return EXCMG_OK;
     const size_t cell_bytes = std::max((size_t)16, plan.exchange), slot_bytes = 6 * 256 * 16;
-    const unsigned steps = (unsigned)std::max(0, hs.maxit - hs.iter) + 3;
-    const bool wrap = c.res_epoch + steps < c.res_epoch;
-    if (wrap || c.res_cells.bytes < cell_bytes || c.res_slots.bytes < slot_bytes) {
-        if (c.res_cells.ensure(cell_bytes) != EXCMG_OK || c.res_slots.ensure(slot_bytes) != EXCMG_OK) {
-            g_err[0] = 0;      // (no room: the sweeps need none)
-            c.res_off = true;
-            return EXCMG_OK;
-        }
-        CKH(hipMemsetAsync(c.res_cells.p, 0, c.res_cells.bytes, g_stream));
-        CKH(hipMemsetAsync(c.res_slots.p, 0, c.res_slots.bytes, g_stream));
-        c.res_epoch = wrap ? 0 : (unsigned)g_res.number;
-    }
+    // an odd number of iterations leaves the directions where the next launch looks for them
+    const int turn = g_res.turn > 0 ? (int)g_res.turn : (int)std::max(1.0, kResidentTurn / plan.us) | 1;
     ResidentRun<T> run{};
     run.n = L.n;
     run.nbx = plan.nbx;
@@ -790,46 +788,76 @@ int bicg_resident(const Level &L, double *x, BicgState &hs, bool *done) {
         run.p[k] = c.p[k].as<T>();
         run.ps[k] = c.ps[k].as<T>();
     }
+    // (q and q* are not kept by a resident run; ubest is of mixed levels, whose vectors are FP32)
+    run.r_out = c.qs.as<T>();
+    run.rs_out = sizeof(T) == 8 ? c.ubest.as<T>() : c.qs.as<T>() + L.nu;
     run.x = x;
     run.x_work = c.q.as<double>();
     run.state = c.state.as<BicgState>();
-    run.cells = c.res_cells.p;
-    run.slots = c.res_slots.p;
-    run.epoch = c.res_epoch;
     run.one_xcd = plan.one_xcd;
     run.look = plan.look;
-    run.wait = resident_wait(0);
-    // a resumed run: rho and r.r of the replaced residual, and whether it stops there (decided
-    // ahead of the launch, whose workgroups could not agree on it without an exchange; the
-    // sweeps, if they take over, repeat it with the same result)
-    if (hs.iter > 0) CKR(close_window<T>(L, hs.iter, g_stream));
-    if (!resident_launch([&] { return resident_run<T>(plan, run, g_stream); })) {
-        c.res_off = true;
-        return EXCMG_OK;
-    }
-    const int iter0 = hs.iter;
-    BicgState now;
-    CKR(read_state(now));
-    if (now.err) {
-        // a wait ran out (the device was not the run's own): the launch-per-sweep form from
-        // here on.  x, r and r* are as they were; a resumed run's directions may not be, and
-        // it ends as a breakdown does, which starts a fresh run
-        c.res_off = true;
-        g_res.gave_up++;
-        if (hs.iter > 0) {
-            hs.status = kBreakdown;
-            *done = true;
+    run.max_steps = (unsigned)turn + (plan.one_xcd ? 1 : 0);
+    for (bool again = false;; again = true) {
+        const unsigned steps = (unsigned)std::min(turn, std::max(0, hs.maxit - hs.iter)) + 3;
+        const bool wrap = c.res_epoch + steps < c.res_epoch;
+        if (wrap || c.res_cells.bytes < cell_bytes || c.res_slots.bytes < slot_bytes) {
+            if (c.res_cells.ensure(cell_bytes) != EXCMG_OK || c.res_slots.ensure(slot_bytes) != EXCMG_OK) {
+                g_err[0] = 0;      // (no room: the sweeps need none)
+                c.res_off = true;
+                return EXCMG_OK;
+            }
+            CKH(hipMemsetAsync(c.res_cells.p, 0, c.res_cells.bytes, g_stream));
+            CKH(hipMemsetAsync(c.res_slots.p, 0, c.res_slots.bytes, g_stream));
+            c.res_epoch = wrap ? 0 : (unsigned)g_res.number;
         }
-        hs.err = 0;
-        *c.host_state = hs;
-        CKH(hipMemcpyAsync(c.state.p, c.host_state, sizeof(BicgState), hipMemcpyHostToDevice,
-                           g_stream));
-        CKH(hipStreamSynchronize(g_stream));
-        return EXCMG_OK;
+        run.cells = c.res_cells.p;
+        run.slots = c.res_slots.p;
+        run.epoch = c.res_epoch;
+        const int cur = hs.iter & 1, other = cur ^ 1;
+        run.p_out = run.p[other];
+        run.ps_out = run.ps[other];
+        run.wait = resident_wait(0);
+        const bool made = resident_launch([&] { return resident_run<T>(plan, run, g_stream); });
+        BicgState now = hs;
+        if (made) CKR(read_state(now));
+        if (!made || now.err) {
+            c.res_off = true;
+            if (made) {      // (a wait ran out: the device was not the run's own)
+                g_res.gave_up++;
+                *c.host_state = hs;
+                CKH(hipMemcpyAsync(c.state.p, c.host_state, sizeof(BicgState), hipMemcpyHostToDevice,
+                                   g_stream));
+                CKH(hipStreamSynchronize(g_stream));
+            }
+            if (again) {     // the first sweep A looks for rho and r.r in partials
+                const int count = b_partials<double, T>(L);
+                Pair *part = c.part_b.as<Pair>();
+                c.host_scal[0] = hs.rho;
+                c.host_scal[1] = hs.rr;
+                CKH(hipMemsetAsync(part, 0, 2 * (size_t)count * sizeof(Pair), g_stream));
+                for (int k = 0; k < 2; k++)
+                    CKH(hipMemcpyAsync(&part[k * count].s, c.host_scal + k, sizeof(double),
+                                       hipMemcpyHostToDevice, g_stream));
+                CKH(hipStreamSynchronize(g_stream));
+            }
+            return EXCMG_OK;
+        }
+        const int made_its = now.iter - hs.iter;
+        c.res_epoch += (unsigned)made_its + 3;
+        const bool halted = now.status == kRunning;
+        if (made_its > 0) {
+            // (FP32 runs may be resumed when they have stopped)
+            const bool dirs = (halted || sizeof(T) == 4) && made_its % 2 == 0;
+            CKH(resident_take(L.nu,
+                              ResidentTake<T>{x, run.x_work,
+                                              {dirs ? run.p[cur] : nullptr, dirs ? run.ps[cur] : nullptr,
+                                               halted ? run.r : nullptr, halted ? run.rs : nullptr},
+                                              {run.p_out, run.ps_out, run.r_out, run.rs_out}},
+                              g_stream));
+        }
+        hs = now;
+        if (!halted) break;
     }
-    c.res_epoch += (unsigned)(now.iter - iter0) + 3;
-    if (now.iter > iter0) CKH((copy_convert<double, double>(L.nu, run.x_work, x, g_stream)));
-    hs = now;
     *done = true;
     return EXCMG_OK;
 }
@@ -845,6 +873,7 @@ int bicg_iterate(const Level &L, TX *x, BicgState &hs, long long &j) {
     bool done = false;
     if constexpr (sizeof(TX) == 8) CKR(bicg_resident<T>(L, x, hs, &done));
     if (done) return EXCMG_OK;
+    j = hs.iter;      // (resident launches may have come before the one that was not made)
     int K = poll_interval(L.nu, g_ctx.dim);
     K += K & 1;
     if (g_timing) CKR(ensure_events(4 * (size_t)(K + 1)));
@@ -1240,7 +1269,8 @@ int level_solve_reliable(const Level &L, const double *b, double *u, double eps,
             since_start++;
             CKH(rho_partials<float>(L.nu, r, rs, c.part_b.as<Pair>(), g_stream, nullptr, rows,
                                     b_partials<double, float>(L)));
-            CKH(state_resume(S, std::max((delta * delta) * rr, 0.25 * target), g_stream));
+            CKH(step_resume(step_link<float>(L, hs.iter), std::max((delta * delta) * rr, 0.25 * target),
+                            g_stream));
             CKR(read_state(hs));
             // the run stopped inside the last window: go on from the iteration it reached
             // (that index selects the direction buffers and the rho slots)
@@ -3114,6 +3144,10 @@ int excmg_resident_control(int what, long long value) {
         case EXCMG_RESIDENT_NUMBER:
             if (value < 0 || value > 0xffffffffll) return fail(EXCMG_EINVAL, "number out of range");
             g_res.number = value;
+            return EXCMG_OK;
+        case EXCMG_RESIDENT_TURN:
+            if (value < 0 || value > (1 << 30)) return fail(EXCMG_EINVAL, "turn out of range");
+            g_res.turn = value;
             return EXCMG_OK;
         default: return fail(EXCMG_EINVAL, "no such control");
     }

@@ -173,6 +173,9 @@ hipError_t cg_update(long long n, const BicgState *s, TX *x, const T *p, T *r, c
 // the end-of-iteration checks of a folded step as a kernel of its own (one workgroup), run
 // before the host reads the state
 hipError_t step_check(StepLink link, hipStream_t st);
+// A run resumed at iteration link.par (mod 2), its residuals replaced: the new threshold, rho and
+// r.r from their partials, and whether the run stops there (its first sweep A repeats the same).
+hipError_t step_resume(StepLink link, double thr, hipStream_t st);
 // partials of rs.r and r.r in the layout of bicg_update's (after a residual replacement);
 // with d, of rs.(r / d) and r.r
 template <typename T>
@@ -230,18 +233,22 @@ struct ResidentRun {
     int n, nbx, nby, bx, by, bz;
     double sgn;                    // fictitious-point sign (Geom::sgn)
     T *r, *rs;                     // residuals at the start (or at a resumption)
-    T *p[2], *ps[2];               // directions: read at a resumption, written at the end
+    T *p[2], *ps[2];               // directions, read if the run goes on (by the iteration's parity)
+    // where a run of its own leaves its directions and, halted, its residuals: none of its
+    // inputs, so a launch that gives up has changed nothing (a batch's runs write their inputs)
+    T *p_out, *ps_out, *r_out, *rs_out;
     const double *x;               // iterate at the start
     double *x_work;                // iterate of the run (the caller's is left alone)
-    BicgState *state;              // as bicg_start left it, or (resumption) step_check or batch_resume
+    BicgState *state;              // as bicg_start, step_resume or batch_resume left it
     void *cells;                   // exchanged cells (ResidentPlan::exchange bytes)
     void *slots;                   // exchanged partials: 6 planes of 16 bytes per workgroup (256)
     unsigned epoch;                // the run's exchanges are numbered from epoch + 1
     bool one_xcd;                  // ResidentPlan::one_xcd
     int look;                      // ResidentPlan::look
     unsigned long long wait;       // longest wait for other workgroups (ticks of 10 ns)
-    // a run of a batch (r and r* are also written when it is halted; x_work may be x)
-    unsigned min_steps, max_steps; // iterations before it may be, and is, halted
+    unsigned max_steps;            // exchanges (one an iteration) after which it is halted
+    // a run of a batch (x_work may be x)
+    unsigned min_steps;            // iterations before it may be halted
     unsigned *stop;                // the launch's: epoch + 1 once a run has stopped
     unsigned *halt;                // this run's: the exchange after which it is halted
 };
@@ -249,6 +256,16 @@ bool resident_plan(int n, int dim, bool fp64, ResidentPlan &plan);
 template <typename T>
 hipError_t resident_run(const ResidentPlan &plan, const ResidentRun<T> &run, hipStream_t st);
 constexpr unsigned long long kResidentWait = 200000000ull;    // 2 s
+// What a launch left, put where the run's inputs are (to[k] == nullptr: not needed).
+template <typename T>
+struct ResidentTake {
+    double *x;
+    const double *x_from;
+    T *to[4];
+    const T *from[4];
+};
+template <typename T>
+hipError_t resident_take(long long n, const ResidentTake<T> &t, hipStream_t st);
 
 // Several 3D runs in one cooperative launch, each on its share of the workgroups.
 constexpr int kBatchShares = 6;

@@ -352,6 +352,25 @@ hipError_t state_resume(BicgState *s, double thr, hipStream_t st) {
     return hipGetLastError();
 }
 
+__global__ void __launch_bounds__(kReduceThreads) k_step_resume(StepLink link, double thr) {
+    __shared__ Pair sh[2 * (kReduceThreads / kWave)];
+    BicgState *s = link.state;
+    const bool runs = s->iter < s->maxit;     // (nothing written below changes it)
+    if (threadIdx.x == 0) {
+        s->thr = thr;
+        s->status = s->poll_status = runs ? kRunning : kNoConv;
+    }
+    __threadfence_block();
+    __syncthreads();
+    double beta;
+    if (runs) (void)link_step(link, beta, sh);
+}
+
+hipError_t step_resume(StepLink link, double thr, hipStream_t st) {
+    hipLaunchKernelGGL(k_step_resume, dim3(1), dim3(kReduceThreads), 0, st, link, thr);
+    return hipGetLastError();
+}
+
 __global__ void __launch_bounds__(kReduceThreads) k_step_check(StepLink link) {
     __shared__ Pair sh[2 * (kReduceThreads / kWave)];
     if (!block_running(&link.state->status)) return;
@@ -441,6 +460,25 @@ template hipError_t copy_convert<double, double>(long long, const double *, doub
 template hipError_t copy_convert<float, double>(long long, const double *, float *, hipStream_t);
 template hipError_t copy_convert<double, float>(long long, const float *, double *, hipStream_t);
 template hipError_t copy_convert<float, float>(long long, const float *, float *, hipStream_t);
+
+template <typename T>
+__global__ void k_resident_take(long long n, ResidentTake<T> t) {
+    const long long stride = (long long)gridDim.x * blockDim.x;
+    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
+        t.x[i] = t.x_from[i];
+#pragma unroll
+        for (int k = 0; k < 4; k++)
+            if (t.to[k]) t.to[k][i] = t.from[k][i];
+    }
+}
+
+template <typename T>
+hipError_t resident_take(long long n, const ResidentTake<T> &t, hipStream_t st) {
+    hipLaunchKernelGGL(k_resident_take<T>, dim3(vec_blocks(n)), dim3(kVecThreads), 0, st, n, t);
+    return hipGetLastError();
+}
+template hipError_t resident_take<float>(long long, const ResidentTake<float> &, hipStream_t);
+template hipError_t resident_take<double>(long long, const ResidentTake<double> &, hipStream_t);
 
 // ------------------------------------------------------------------ finalisation
 

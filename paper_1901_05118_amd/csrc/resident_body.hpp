@@ -489,17 +489,19 @@
         else if (iter >= maxit) status = kNoConv;
         else if (rho == 0.0 || !isfinite(rho)) status = kBreakdown;
         beta = wave_uniform(rho / rho_old);
-        // (written before the partials of this iteration were sent, so every workgroup of the
-        // run reads the same, and not overwritten before all have sent their next sigma)
-        if (BATCH && halted == ep) break;
+        // (halt: written before the partials of this iteration were sent, so every workgroup of
+        // the run reads the same, and not overwritten before all have sent their next sigma)
+        if (BATCH ? halted == ep : ep - a.epoch >= a.max_steps) break;
     }
     if (MULTI && bad) {
         if (tid == 0) atomicExch(&S->err, 1);
         return;
     }
-    // the iterate, and the directions for a run that goes on after its residuals are replaced
+    // the iterate, the directions for a run that goes on after its residuals are replaced, and
+    // all of the state of a run that is halted
     {
-        T *p = a.p[iter & 1], *ps = a.ps[iter & 1];
+        T *p = BATCH ? a.p[iter & 1] : a.p_out, *ps = BATCH ? a.ps[iter & 1] : a.ps_out;
+        T *r_out = BATCH ? a.r : a.r_out, *rs_out = BATCH ? a.rs : a.rs_out;
 #pragma unroll
         for (int c = 0; c < C; c++) {
             if (c < cells) {
@@ -507,9 +509,9 @@
                 if (!kLean) a.x_work[i] = xv[kLean ? 0 : c];
                 p[i] = o[c];
                 ps[i] = M[ob + c * PS];
-                if (BATCH && status == kRunning) {
-                    a.r[i] = r[c];
-                    a.rs[i] = s[c];
+                if (status == kRunning) {
+                    r_out[i] = r[c];
+                    rs_out[i] = s[c];
                 }
             }
         }

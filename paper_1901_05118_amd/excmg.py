@@ -407,12 +407,13 @@ def get_timing(level: int, sweep: int):
     return ms.value, n.value
 
 
-RESIDENT_CONTROLS = {"refuse": 1, "expire": 2, "problem": 3, "wait": 4, "number": 5}
+RESIDENT_CONTROLS = {"refuse": 1, "expire": 2, "problem": 3, "wait": 4, "number": 5,
+                     "turn": 6}
 
 
 def resident_control(**controls: int):
     """Reset the control of the resident launches and their counts, then set the given ones:
-    refuse, expire, problem, wait, number (see excmg_resident_control)."""
+    refuse, expire, problem, wait, number, turn (see excmg_resident_control)."""
     fn = load().excmg_resident_control
     _check("excmg_resident_control", fn(0, 0))
     for name, value in controls.items():

@@ -89,6 +89,133 @@ def test_refused_launches_of_fresh_and_resumed_runs(ex):
         np.testing.assert_array_equal(v, u)
 
 
+@pytest.mark.parametrize("turn", [1, 4, 5])
+@pytest.mark.parametrize("N,levels,bc", [(8, 3, 1), (16, 3, 1), (40, 4, 2), (96, 6, 1), (128, 6, 2)])
+def test_halted_run_goes_on(ex, N, levels, bc, turn):
+    """A run halted after every `turn` iterations: even and odd ones (which pair of buffers holds
+    the directions), the last launch not a whole one."""
+    print(f"halted N={N} bc={bc} turn={turn}", flush=True)
+    ex.setup(N, levels, bc)
+    rng = np.random.default_rng(N)
+    b, x0 = rng.standard_normal((2, (N - 1) ** 3))
+    its = 11 if N < 128 else 6
+    xr, itr, rrr, rcr = O.bicg(N, bc, b, x0, 0.0, maxit=its)
+    ex.resident_control(turn=turn)
+    x = dev(x0)
+    rc, it, rr = ex.bicg(levels - 1, dev(b), x, 0.0, its)
+    assert (rc, it, rr) == (ex.ENOCONV, its, rrr)
+    np.testing.assert_array_equal(x.cpu().numpy(), xr)
+    assert ex.resident_counts() == (-(-its // turn), 0)
+
+
+@pytest.mark.parametrize("turn", [4, 5])
+@pytest.mark.parametrize("N,levels", [(64, 5), (512, 6)])
+def test_halted_plane_run_goes_on(ex, N, levels, turn):
+    ex.setup_2d(N, levels, 1)
+    rng = np.random.default_rng(N)
+    b, x0 = rng.standard_normal((2, (N - 1) ** 2))
+    xr, itr, rrr, rcr = O.bicg_2d(N, 1, b, x0, 0.0, maxit=11)
+    ex.resident_control(turn=turn)
+    x = dev(x0)
+    assert ex.bicg(levels - 1, dev(b), x, 0.0, 11) == (ex.ENOCONV, 11, rrr)
+    np.testing.assert_array_equal(x.cpu().numpy(), xr)
+    assert ex.resident_counts() == (3, 0)
+
+
+def test_a_long_run_lets_others_in(ex):
+    """A launch holds the chip, so a long run takes several (20 ms of iterations each, some 4000 on
+    this plane)."""
+    N, levels = 256, 7
+    ex.setup_2d(N, levels, 1)
+    b = dev(np.random.default_rng(1).standard_normal((N - 1) ** 2))
+    x = torch.zeros_like(b)
+    rc, it, rr = ex.bicg(levels - 1, b, x, 1e-200, 20000)
+    made, gave_up = ex.resident_counts()
+    print(f"{it} iterations in {made} launches", flush=True)
+    assert rc == ex.ENOCONV and it == 20000
+    assert gave_up == 0 and 3 <= made <= 10
+
+
+# `wait` 0: given up at the first exchange that a workgroup has to wait for; longer ones: later,
+# and perhaps not by all workgroups.  turn 1 ends most launches in their last exchange.
+@pytest.mark.parametrize("turn", [1, 4, 5])
+@pytest.mark.parametrize("wait", [0, 120, 250])
+@pytest.mark.parametrize("N,levels,bc", [(16, 3, 2), (48, 5, 1), (112, 5, 2)])
+def test_run_that_gives_up_on_the_way(ex, N, levels, bc, turn, wait):
+    print(f"give up on the way N={N} turn={turn} wait={wait}", flush=True)
+    ex.setup(N, levels, bc)
+    rng = np.random.default_rng(N)
+    b, x0 = rng.standard_normal((2, (N - 1) ** 3))
+    its = 11
+    xr, itr, rrr, rcr = O.bicg(N, bc, b, x0, 0.0, maxit=its)
+    for launch in (1, 2) if turn < 5 else (1,):
+        ex.finalize()
+        ex.setup(N, levels, bc)
+        ex.resident_control(turn=turn, expire=launch, wait=wait)
+        x = dev(x0)
+        rc, it, rr = ex.bicg(levels - 1, dev(b), x, 0.0, its)
+        assert (rc, it, rr) == (ex.ENOCONV, its, rrr)
+        np.testing.assert_array_equal(x.cpu().numpy(), xr)
+        if wait == 0:
+            assert ex.resident_counts() == (launch + 1, 1)
+
+
+@pytest.mark.parametrize("turn", [0, 7, 8])
+def test_mixed_run_that_gives_up(ex, turn):
+    """FP32 vectors: fresh, resumed and halted runs that give up equal the sweeps."""
+    N, levels, bc = 40, 4, 1
+    ex.resident_control(refuse=0)
+    u, its = _mixed(ex, N, levels, bc)
+    for launch in (None, 0, 1, 2, 3, 5, 8):
+        print(f"mixed: launch {launch} gives up", flush=True)
+        ex.finalize()
+        ex.resident_control(turn=turn, **({} if launch is None else dict(expire=launch)))
+        v, n = _mixed(ex, N, levels, bc)
+        made, gave_up = ex.resident_counts()
+        assert gave_up == (launch is not None and launch < made)
+        assert n == its
+        np.testing.assert_array_equal(v, u)
+
+
+def test_mixed_plane_halted(ex):
+    from manufactured.twod import family_2d, make_arrays_2d
+    N, levels, bc = 96, 5, 1
+    arr = make_arrays_2d(family_2d(5), N, bc)
+    f, g1, g2 = dev(arr.f), dev(arr.g1), dev(arr.g2)
+    got = []
+    for control in (dict(refuse=0), dict(turn=8), dict(turn=9, expire=7)):
+        ex.finalize()
+        ex.resident_control(**control)
+        u = torch.empty_like(f)
+        rc, st = ex.solve_ex_2d(N, levels, bc, f, g1, g2, 1e-9, u, precision=ex.MIXED,
+                                fp32_min_unknowns=1)
+        assert rc == ex.OK, ex.last_error()
+        got.append((u.cpu().numpy(), [(s["iterations"], s["runs"]) for s in st.levels()]))
+    for v, n in got[1:]:
+        assert n == got[0][1]
+        np.testing.assert_array_equal(v, got[0][0])
+
+
+def test_run_with_a_shadow_residual(ex):
+    """A given shadow residual (r*_0 alone: M = I, no dual iterate) runs resident, halted or not."""
+    N, levels, bc = 40, 4, 1
+    rng = np.random.default_rng(5)
+    b, x0, s = rng.standard_normal((3, (N - 1) ** 3))
+    got = []
+    for control in (dict(refuse=0), {}, dict(turn=4), dict(turn=4, expire=1)):
+        ex.finalize()
+        ex.setup(N, levels, bc)
+        ex.resident_control(**control)
+        x = dev(x0)
+        rc, it, rr = ex.bicg_ex(levels - 1, dev(b), x, 0.0, 11, shadow=dev(s))
+        assert (rc, it) == (ex.ENOCONV, 11)
+        assert ex.resident_counts()[0] > 0
+        got.append((rr, x.cpu().numpy()))
+    for rr, x in got[1:]:
+        assert rr == got[0][0]
+        np.testing.assert_array_equal(x, got[0][1])
+
+
 def test_resumed_run_with_nothing_to_do(ex):
     """inner_tol 2: every replaced residual is below its threshold at once, so a resumed run stops
     before its first iteration and leaves the iterate alone."""
