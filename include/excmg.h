@@ -323,7 +323,7 @@ int excmg_get_timing(int level, int sweep, double *ms_total, long long *launches
  *   EXCMG_RESIDENT_PROBLEM  ... for the run of problem `value` of a batch alone (-1: all)
  *   EXCMG_RESIDENT_WAIT     ticks of 10 ns (0: one look)
  *   EXCMG_RESIDENT_NUMBER   number that the exchanges of a new context or batch start from
- *   EXCMG_RESIDENT_TURN     iterations of a single run per launch (0: about 20 ms of them)
+ *   EXCMG_RESIDENT_TURN     iterations of a run per launch at most (0: about 20 ms of them)
  * excmg_resident_counts: launches since then, and those refused or given up. */
 #define EXCMG_RESIDENT_RESET 0
 #define EXCMG_RESIDENT_REFUSE 1

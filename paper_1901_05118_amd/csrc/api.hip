@@ -1525,6 +1525,10 @@ struct StepSet {
 
 // The running systems of a batch whose vectors fit on the chip, as many of them at a time as
 // there are CUs for, in one resident launch (resident.hip).
+// Whether a wait ran out in a batch: the device is not the library's own, and later batches do
+// not try (each would wait for 2 s), until excmg_finalize.
+bool g_batch_waits = false;
+
 struct ResidentSet {
     struct Plans {
         int n;
@@ -1535,7 +1539,7 @@ struct ResidentSet {
     DBuf table, cells, slots, flags;
     ResidentBatchRun *h_table = nullptr;
     unsigned epoch = 0;
-    bool off = false;              // (a wait ran out, or no room: the steps take all systems)
+    bool off = g_batch_waits;      // (a wait ran out, or no room: the steps take all systems)
     std::vector<int> now;          // systems of the launch in flight
     ~ResidentSet() {
         table.release(); cells.release(); slots.release(); flags.release();
@@ -1932,8 +1936,8 @@ struct BatchSolver {
     // goes to those with the slowest iterations.  (Small shares: a system on twice the CUs is
     // less than twice as fast, so they finish more systems per second, and the large ones are
     // the last to be alone.)  A launch ends when one of its runs has stopped, but not before
-    // kBatchWindow, so that stops and restarts come together, nor, with `others` waiting for
-    // steps, after kBatchTurn.
+    // kBatchWindow, so that stops and restarts come together, nor after kBatchTurn with `others`
+    // waiting for steps, kResidentTurn without (see there).
     static constexpr double kBatchWindow = 500.0, kBatchTurn = 4000.0;   // us
     int launch_resident(bool others) {
         res.now.clear();
@@ -2038,7 +2042,8 @@ struct BatchSolver {
             R.look = P.look;
             R.wait = resident_wait(run[k].j);
             R.min_steps = (unsigned)std::max(1.0, kBatchWindow / P.us);
-            R.max_steps = others ? (unsigned)std::max(1.0, kBatchTurn / P.us) : ~0u;
+            R.max_steps = g_res.turn > 0 ? (unsigned)g_res.turn
+                                         : (unsigned)std::max(1.0, (others ? kBatchTurn : kResidentTurn) / P.us);
             R.stop = res.flags.as<unsigned>();
             R.halt = res.flags.as<unsigned>() + 1 + k;
             blocks += P.blocks;
@@ -2072,6 +2077,7 @@ struct BatchSolver {
                 late = true;
                 b.phase = kPhaseCheck;
                 b.prev = INFINITY;
+                b.iters += std::max(0, h_states[j].iter - b.iter_base);
                 h_states[j].err = 0;
                 h_states[j].status = kBreakdown;
                 CKH(hipMemcpyAsync(S(j), &h_states[j], sizeof(BicgState), hipMemcpyHostToDevice, st));
@@ -2083,6 +2089,7 @@ struct BatchSolver {
         res.epoch += used + 2;
         if (!late) return EXCMG_OK;
         g_res.gave_up++;
+        g_batch_waits = true;
         return resident_stop();
     }
 
@@ -3168,6 +3175,7 @@ void excmg_finalize(void) {
         std::lock_guard<std::mutex> turn(g_exp_mutex);
         g_exp_scratch.release();
     }
+    g_batch_waits = false;
     g_ctx.release();
 }
 

@@ -317,3 +317,38 @@ def test_batch_exchange_numbers_wrap(ex):
     assert got[1] == want[1]
     for a, b in zip(got[0], want[0]):
         np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("case", ["fp64", "fp32"])
+def test_batch_runs_halted_by_their_turn(ex, case):
+    want = _batch(ex, SIZES, persistent=True, **_options(ex, case))
+    ex.resident_control(turn=50)
+    got = _batch(ex, SIZES, **_options(ex, case))
+    longest = max(sum(n for n, _, _ in its) for its in got[1])
+    made, gave_up = ex.resident_counts()
+    assert made >= longest / 50 and gave_up == 0
+    assert got[1] == want[1]
+    for a, b in zip(got[0], want[0]):
+        np.testing.assert_array_equal(a, b)
+
+
+def test_batch_that_gave_up(ex):
+    """The iterations of the run that gave up count, and no later batch waits again."""
+    N, nl = 64, 5
+    arr = make_arrays(config_problem(2), N, 1)
+    f, g1, g2 = dev(arr.f), dev(arr.g1), dev(arr.g2)
+    prob = dict(n_finest=N, n_levels=nl, bc_kind=1, f=f, g1=g1, g2=g2, u_out=torch.empty_like(f))
+
+    def level2():
+        rc, stats = ex.solve_batch([prob], 1e-12, max_iters=60, max_runs=1)
+        assert rc == ex.ENOCONV
+        return stats[0].levels()[2]["iterations"]
+
+    ex.resident_control(turn=20, expire=1)
+    assert level2() == 20 + 60            # 20 resident, then a fresh run by steps
+    assert ex.resident_counts() == (2, 1)
+    assert level2() == 60
+    assert ex.resident_counts() == (2, 1)
+    ex.finalize()
+    assert level2() == 60
+    assert ex.resident_counts()[0] > 2
