@@ -371,8 +371,10 @@ __global__ void __launch_bounds__(MT) k_resident(ResidentRun<T> a) {
 
 template <int DIM, typename T, int C, int RS, int NH, int MT>
 hipError_t launch_resident(const ResidentPlan &pl, ResidentRun<T> run, hipStream_t st) {
-    const void *fn = pl.blocks > 1 ? (const void *)k_resident<DIM, T, C, RS, NH, MT, true>
-                                   : (const void *)k_resident<DIM, T, C, RS, NH, MT, false>;
+    const void *fn = (const void *)k_resident<DIM, T, C, RS, NH, MT, true>;
+    if constexpr (sizeof(T) == 4 || C < 16) {      // (the lean kernel is of several bricks only)
+        if (pl.blocks == 1) fn = (const void *)k_resident<DIM, T, C, RS, NH, MT, false>;
+    }
     hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)pl.lds);
     if (e != hipSuccess) return e;
     void *args[] = {&run};

@@ -277,7 +277,8 @@
             qv[c] = c < cells ? (T)y : (T)0;
             dot2_acc(sg[0], (double)o[c], (double)qv[c]);
             // (one output after the other)
-            if (C >= 8) asm volatile("" : "+v"(sg[0].s), "+v"(sg[0].c), "+v"(qv[c])); if (kLean) asm volatile("" ::: "memory");
+            if (C >= 8) asm volatile("" : "+v"(sg[0].s), "+v"(sg[0].c), "+v"(qv[c]));
+            if (kLean) asm volatile("" ::: "memory");
         });
         wave_merge_n<1>(sg);
         if (lane == 0) red[wave] = sg[0];
