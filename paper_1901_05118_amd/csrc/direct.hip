@@ -328,6 +328,12 @@ hipError_t band_solve(int n, int w, const double *C, const double *b, double *x,
         hipLaunchKernelGGL((k_band_solve<(NG + 3) / 4, NG, DP>), dim3(1), dim3(64), 0, st, n, w, C, b, x); \
         return hipGetLastError();                                                               \
     }
+    // up to 32 unknowns most of a solve is fetching its code, which chunks of one column keep
+    // short (whole calls, chunks of 8 / of 1: 1 unknown 17.9 / 14.0 us, 9 21.3 / 18.0, 25
+    // 28.6 / 26.2; from 36 on no different)
+    if (n <= 32) {
+        EXCMG_SOLVE(2, 1)
+    }
     EXCMG_SOLVE(2, 8)
     EXCMG_SOLVE(4, 8)
     EXCMG_SOLVE(6, 8)
