@@ -25,6 +25,14 @@
  *    every array it passes; the library keeps no pointer after a call returns.
  *  * Work is issued on the stream set with excmg_set_stream (default: the null stream) and
  *    every entry point returns after its results are complete.
+ *  * Bi-CG on grids of up to 128^3 cells and planes of up to 1024^2 runs resident: a run is one
+ *    or more cooperative launches that hold the GPU for about 20 ms each at most; work on other
+ *    streams gets in between.  If such a launch is refused, or its workgroups wait for each other
+ *    for 2 s (the GPU is shared with something that does not end), the run goes on by launches
+ *    per iteration with the same iterates, and so do later ones: of the context until it is made
+ *    anew, of batches (after a wait) until excmg_finalize.  CG, Jacobi, dual systems, timed runs
+ *    (excmg_set_timing), padded FP32 rows and an explicit recompute_min_unknowns take the
+ *    launches per iteration (the sweeps) on any grid.
  *  * The library holds one context per process (levels, workspace, cached factors).  Calls
  *    are not thread-safe.
  *  * Return codes: EXCMG_OK (0) or a negative code; excmg_last_error() describes the last
@@ -341,7 +349,8 @@ int excmg_resident_counts(long long *launches, long long *gave_up);
  * ty = 4 or 8 for FP64, 4, 8 or 16 for FP32).  ty = 0
  * restores the built-in table (the autotuner's MI355X picks per grid-size band).  Applies to later launches, including levels of the current
  * context.  The autotuner uses it; results do not depend on the shape (every output is
- * computed with the same arithmetic). */
+ * computed with the same arithmetic).  Resident runs (up to 128^3, see above) launch no sweep
+ * A: there kinds 1 and 2 matter to the runs that take the sweeps. */
 int excmg_set_shape(int n, int kind, int ty, int zc);
 int excmg_get_shape(int n, int kind, int *ty, int *zc);
 
@@ -373,11 +382,12 @@ typedef struct excmg_problem {
  * precision and the iteration limits (its n_finest, n_levels and bc_kind are ignored).
  * stats, if not NULL, is an array of nprob records.  Runs on a stream of its own, ordered
  * after the library stream's earlier work.  Tile shapes of the batched sweep A: those
- * recorded by excmg_autotune_batch. */
+ * recorded by excmg_autotune_batch (they matter to systems advanced by steps). */
 int excmg_solve_batch(int nprob, const excmg_problem *probs, const excmg_opts *opts,
                       excmg_stats *stats);
 
-/* Autotuner of the batched Bi-CG step (configuration of excmg_solve_batch): puts the finest
+/* Autotuner of the batched Bi-CG step (of systems advanced by steps: with batch_mode 0 those
+ * beyond 128^3, with batch_mode 1 all): puts the finest
  * level of the batch's problems into running Bi-CG runs and, for tile heights of 4 and 8
  * rows and per distinct grid size, times steps of that size's systems alone (the phase
  * launches, replayed from a captured graph; `reps` graph replays of 8 steps per shape) with

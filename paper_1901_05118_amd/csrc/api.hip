@@ -981,7 +981,6 @@ int bicg_iterate(const Level &L, TX *x, BicgState &hs, long long &j) {
     return EXCMG_OK;
 }
 
-// One Bi-CG run from x (in place) on level L with right-hand side b.
 // One run of Algorithm 2 from x (in place) on level L with right-hand side b.  Options: d,
 // the diagonal of a preconditioner M (NULL: M = I); the shadow system, either bstar and
 // xstar (r*_0 = b* - A^T x*_0, x* updated in place) or shadow (r*_0 = shadow), else

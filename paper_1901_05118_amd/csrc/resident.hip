@@ -4,8 +4,10 @@
 // What bounds the launch-per-sweep form there: two launches per iteration, each with its
 // drain, its dispatch and a merge of the other sweep's partials (9 us a launch on 16^3 and
 // 32^3), and from 64^3 on the vectors' way through the caches.  Here every workgroup owns a
-// brick of the grid (of the plane in 2D, the rows of which are z here) for the whole run: the iterate and r, r*, p, p*, q, q* of its cells stay
-// in registers, the marched array (p, then p*) in LDS with a 2-wide halo.  An iteration
+// brick of the grid (of the plane in 2D, the rows of which are z here) for the whole run: the
+// iterate and r, r*, p, p*, q, q* of its cells stay in registers, the marched array (p, then p*)
+// in LDS with a 2-wide halo.  (FP64 with 16 cells per thread, 112^3 and 128^3: the iterate in
+// memory, q* not kept; see resident_body.hpp.)  An iteration
 // exchanges, all past the L2 (which the XCDs do not share),
 //  * the partials of sigma, and of rho' and r.r (all to all: every workgroup merges all of
 //    them in one order, so all take the same scalars and the same decisions), and
@@ -19,11 +21,11 @@
 // who has all partials may read all cells.  Either is overwritten one iteration later, after
 // a reduction that needed all its readers.
 //
-// What bounds an iteration now (cycles at 2.35 GHz, 64^3 on 128 workgroups, of 21000): the two
-// exchanges (a load past the L2 takes 1800), the two stencils (4600: LDS reads, 16 per
+// What bounds an iteration (64^3, 9.2 us): the two exchanges with the wait for the slowest
+// workgroup (2.9; a load past the L2 takes 1800 cycles), the two stencils (2.4: LDS reads, 16 per
 // output), the directions, the update with its dot products.
 //
-// Measured choices: exchanged cells in mailboxes, contiguous per reader, against cells in
+// Measured choices (each when it was made, on the partition taken then): exchanged cells in mailboxes, contiguous per reader, against cells in
 // grid order, each word proving itself: 64^3 10.6 -> 8.5 us, 96^3 22.3 -> 17.5 us (half the
 // bytes and whole lines: what the CUs can load past the L2 bounds the exchange); q* formed
 // while sigma's partials travel; partials first looked for some time after they are sent
@@ -42,8 +44,8 @@
 // between launch shapes.
 //
 // The workgroups wait for each other, so they are launched cooperatively (one per CU, all
-// resident) and every wait is bounded: past the run's `wait` the launch gives up (err set, the
-// caller's vectors untouched) and the host runs the launch-per-sweep form instead.
+// resident) and every wait is bounded: past the run's `wait` the launch gives up (err set, a
+// single run's vectors untouched) and the host goes on with the launch-per-sweep form.
 #include <algorithm>
 
 #include "common.hpp"
@@ -476,16 +478,19 @@ void for_plans(int n, int dim, bool fp64, bool batch, Use use) {
 }  // namespace
 
 // The partition of an n^3 grid or n^2 plane: the cheapest by a model of an iteration's time
-// (us), fitted to 800 partitions of 3D grids of 12 to 96 cells (FP64; what it picks takes 3%
-// longer than the best of each grid, 9% at most): work per wave and per thread, exchanges that
-// grow with the number of workgroups, cells exchanged.  Measured per iteration against the
-// launch-per-sweep form: 16^3 4.7 / 17.9, 32^3 5.2 / 18.3, 48^3 6.8 / 21.3, 64^3 9.4 / 26.1,
-// 96^3 15.8 / 45.0 us.  FP32 vectors: 96^3 13.4 / 37.3, 112^3 20.1 / 48.9, 128^3 (8192 cells
-// per workgroup, 16 per thread) 22 / 45.  Planes, FP64: 128^2 3.9 / 12.1, 256^2 4.9 / 13.3,
-// 512^2 6.4 / 24.2, 1024^2 (whole run of 15) 24 / 64.
-// FP64 with 16 cells per thread (112^3, 128^3): 32.9 / 46.9, 37.5 / 51.4; half of it is what
+// (us), fitted to 800 partitions of 3D grids of 12 to 96 cells in FP64: work per wave and per
+// thread, exchanges that grow with the number of workgroups, cells exchanged.  FP32, planes (half
+// the terms a cell) and 16 cells per thread (8 us more) take it with those constants; against the
+// best of the 28 cheapest partitions, all timed, what it picks takes longer by: FP64 32^3 9%, 64^3
+// 6%, 96^3 0, 112^3 1%, 128^3 0; FP32 32^3 2%, 64^3 4%, 96^3 1%, 112^3 0, 128^3 4%; planes 128^2
+// 0, 256^2 2%, 512^2 and 1024^2 0.
+// Measured per iteration against the launch-per-sweep form: 16^3 4.1 / 17.9, 32^3 5.2 / 18.3,
+// 48^3 6.5 / 21.3, 64^3 9.2 / 26.1, 96^3 15.7 / 45.0 us.  FP32 vectors: 96^3 13.4 / 37.3, 112^3
+// 20.1 / 48.9, 128^3 (8192 cells per workgroup, 16 per thread) 22 / 45.  Planes, FP64: 128^2 3.8 /
+// 12.1, 256^2 4.9 / 13.3, 512^2 6.4 / 24.2, 1024^2 9.1 / 64.
+// FP64 with 16 cells per thread (112^3, 128^3): 31.3 / 46.9, 35.6 / 51.4; half of it is what
 // goes past the L2 (the iterate, 33 MB an iteration, and the halo, 44 MB, at about 4.5 TB/s),
-// and it still spills 38 registers.  Planes above about 1000^2 do not fit; smaller grids are
+// and 26 registers are in scratch memory.  Planes above 1024^2 are not tried; smaller grids are
 // levels solved directly.
 bool resident_plan(int n, int dim, bool fp64, ResidentPlan &plan) {
     plan.us = 1e30;
@@ -562,7 +567,8 @@ __device__ __forceinline__ void batch_run(const EXCMG_CONSTANT ResidentRun<T> &a
 // workgroup's remaining waves only).  24 problems of 32^3 to 128^3 in mixed precision: 775 ms
 // by steps of four launches (20 us a step at the least), 312 ms resident, of which 223 in 91
 // launches; one after the other with launches of their own they take 376 ms.  In FP64 830 by
-// steps, 358 resident (480 with the 128^3 systems by steps).
+// steps, 358 resident (480 with the 128^3 systems by steps).  All kinds in one kernel, which has
+// 42 registers in scratch memory (168 bytes a lane; the FP64 kernel with 16 cells alone 26).
 __global__ void __launch_bounds__(512) k_resident_batch(const ResidentBatchRun *table, int count) {
     extern __shared__ char lds_raw[];
     __shared__ ResidentShared sh;

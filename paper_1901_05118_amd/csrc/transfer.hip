@@ -3,15 +3,17 @@
 //
 // Both are bound by HBM: EXP_true reads the fine solution and the coarse one (1/8 of its
 // size) and writes a fine array; EXP_finite writes its fine array from inputs of 1/8 and 1/64
-// of its size.  A workgroup owns a 64 x 8 tile of fine nodes and marches in z, so a node's
+// of its size.  A workgroup owns a tile of fine nodes (128 x 4 for the midpoints, 64 x 16 for the
+// interpolation) and marches in z, so a node's
 // place is found once, a plane's coarse values are staged once in LDS (with the coarse nodes
 // on the tile's far sides), and every fine value is read and written once, in rows.  One
 // barrier per step: the staged planes are a ring long enough that a step's writes miss what
 // the step before still reads, and the next step's loads are in flight meanwhile.  Measured,
 // whole calls, against one thread per node with its neighbours from global memory: EXP_true
 // at 512^3 1361 -> 512 us (4.5 TB/s of the bytes it must move), at 256^3 189 -> 92 us;
-// EXP_finite at 256^3 381 -> 86 us (of the 381, its two kernels took 300, an allocation and a
-// free of the intermediate grid the rest), at 128^3 105 -> 35 us.
+// EXP_finite at 256^3 381 -> 64 us on one set of arrays, 82 on new ones (of the 381, its two
+// kernels took 300, an allocation and a free of the intermediate grid the rest), at 128^3 100 ->
+// 27 us, at 512^3 2862 -> 890.
 //
 // Every formula is evaluated in the order it is written in (contraction off).
 #include <algorithm>
